@@ -144,7 +144,7 @@ dppo_status check_matrix(const void* p, int32_t dtype, int64_t T, int64_t V, int
 }
 
 struct LmhLayout {
-  int64_t part, zy, w, lse2, dy, ev, g, total;  // byte offsets into the workspace, and its size
+  int64_t part, w, lse2, dy, ev, g, total;  // byte offsets into the workspace, and its size
   int64_t chunk, ldg;                        // vocabulary rows per backward chunk, g's stride
   bool one_pass;                             // G from the forward tiles' exponentials
 };
@@ -166,7 +166,7 @@ LmhLayout lmh_layout(int64_t T, int64_t V, int64_t vocab_chunk) {
   L.ldg = chunk;
   int64_t o = 0;
   L.part = o; o = align256(o + ngroups * T * 2 * 4);
-  L.zy = o;   o = align256(o + T * 4);
+  o = align256(o + T * 4);                  // unused (z[y] had a vector here): the size stays
   L.w = o;    o = align256(o + T * 4);
   L.lse2 = o; o = align256(o + T * 4);
   L.dy = o;   o = align256(o + T * 4);
@@ -558,7 +558,6 @@ dppo_status fused_lm_head_loss_fwd_bwd(
     m.n0 = 0;
     m.n1 = (int32_t)V;
     m.part = (float*)(ws + L.part);
-    m.zy = (float*)(ws + L.zy);
     m.w = (float*)(ws + L.w);
     m.lse2 = (float*)(ws + L.lse2);
     m.dy = (float*)(ws + L.dy);
@@ -638,16 +637,17 @@ dppo_status fused_lm_head_loss_fwd_bwd(
       }
       return DPPO_OK;
     };
-    if ((e = dppo::launch_lmh_zy(m, st)) != hipSuccess) return hip_fail(e, "z_y launch");
     if ((e = timed([&] { return dppo::launch_lmh_fwd_tiles(m, st); })) != hipSuccess)
       return hip_fail(e, "forward tile launch");
+    // with flags the loss sum derives the counters from them
+    if ((e = dppo::launch_lmh_tokens(a, m, flags_out == nullptr, st)) != hipSuccess)
+      return hip_fail(e, "token launch");
     if (m.store_p) {
-      // one pass: the row pass finishes every token, the scale pass forms G in place
-      if ((e = dppo::launch_lmh_grad_rows(a, m, st)) != hipSuccess) return hip_fail(e, "gradient row launch");
+      // one pass: the scale pass forms G in place
+      if ((e = dppo::launch_lmh_grad_scale(m, st)) != hipSuccess) return hip_fail(e, "gradient scale launch");
       s = products(0, V);
       if (s != DPPO_OK) return s;
     } else {
-      if ((e = dppo::launch_lmh_finish(a, m, st)) != hipSuccess) return hip_fail(e, "finish launch");
       for (int64_t n0 = 0; grads && n0 < V; n0 += L.chunk) {
         const int64_t n1 = std::min<int64_t>(V, n0 + L.chunk);
         m.n0 = (int32_t)n0;
@@ -660,7 +660,7 @@ dppo_status fused_lm_head_loss_fwd_bwd(
     }
   }
   dppo::launch_loss_sum(loss_tok_out, loss_mask, token_scale, stats_out, T, p->loss_scale,
-                        p->scale_mode, loss_out, st);
+                        p->scale_mode, loss_out, st, T > 0 ? flags_out : nullptr, p->rd_mode);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "loss_sum launch");
   return DPPO_OK;

@@ -32,7 +32,6 @@ struct LmhArgs {
   float* part;             // forward: (m2, sum 2^(z log2 e - m2)) per (token, group), with
                            // m2 = log2 e * the group's maximum; [T][groups] float pairs, so a
                            // token's partials are contiguous for the row pass
-  float* zy;               // z[t, y_t] (dot-product kernel)
   float* w;                // MIS weight per token (0 where the gradient is zero)
   float* lse2;             // log2 sum_v 2^(z log2 e) per token
   float* dy;               // w (p_y - 1) per token: the sampled entry of G (one pass)
@@ -68,12 +67,12 @@ struct GemmArgs {
 };
 constexpr int LMH_GBM = 256, LMH_GBN = 256;  // C tile of one workgroup
 
-hipError_t launch_lmh_zy(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_fwd_tiles(const LmhArgs& m, hipStream_t st);
-hipError_t launch_lmh_finish(const RowArgs& a, const LmhArgs& m, hipStream_t st);
+// count: add the counters to a.stats with atomics (else the loss sum derives them from flags)
+hipError_t launch_lmh_tokens(const RowArgs& a, const LmhArgs& m, bool count, hipStream_t st);
 hipError_t launch_lmh_bwd_tiles(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_zero(float* p, int64_t n, hipStream_t st);  // fill kernel (no memset)
-hipError_t launch_lmh_grad_rows(const RowArgs& a, const LmhArgs& m, hipStream_t st);
+hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_grad_gemm(const GemmArgs& g, bool a_mn, bool b_mn, hipStream_t st);
 
 }  // namespace dppo

@@ -3,13 +3,11 @@
 //   lmh_fwd_tiles  one tile per workgroup on the matrix cores, reduced to per-token partial
 //                  log-sum-exps of each 128-entry vocabulary group; optionally also stores
 //                  the group-normalised exponentials 2^(z log2 e - m2) as fp16;
-//   lmh_zy         z[t, y_t] as one dot product per token;
-//   lmh_row_stats  per token row: merges the partials into lse_t and runs the token math
-//                  of Eq. 1-4 (ratios, band, PPO clip, loss, MIS weight w_t);
+//   lmh_tokens     per token: merges the partials into lse_t, forms z[t, y_t] as a dot
+//                  product and runs the token math of Eq. 1-4 (ratios, band, PPO clip, loss,
+//                  MIS weight w_t);
 //   lmh_grad_scale turns the stored exponentials into G = w_t (softmax - onehot) in bf16,
 //                  the operand of the two gradient products (lm_head_grad.hip);
-//   lmh_finish     the same merge and token math without G (forward only, or the
-//                  vocabulary-chunk mode);
 //   lmh_bwd_tiles  vocabulary-chunk mode: recomputes a tile and writes G for one chunk.
 #include <type_traits>
 #include <utility>
@@ -312,140 +310,100 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_fwd_tiles(LmhArgs m) {
   LMH_RUN_ENGINE(m, m0, r0, epi);
 }
 
-// z[t, y_t] = hidden[t] . weight[y_t]: one wave per token, fp32 accumulation.
-__global__ __launch_bounds__(256) void lmh_zy(LmhArgs m) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+// One wave per token: merges the token's group partials into lse2, forms z[t, y_t] as a dot
+// product of hidden[t] and weight[y_t] (fp32 accumulation), runs the token math (per-token
+// outputs) and leaves the backward constants w, lse2, dy = w (p_y - 1) and ev.
+//
+// Latency-bound (8 bytes per token and group, 4 d bytes per token): a wave's partial and operand
+// loads are issued before anything waits on them, and every token has a wave at once. It
+// replaces a dot-product kernel, a merge with one workgroup per token whose five counter atomics
+// per workgroup serialised (36 us at T = 1024, V = 32000, 103 us at T = 8192, V = 151936) and,
+// in the chunked mode, a merge with one thread per token (515 us at T = 2048, V = 151936). When
+// the call writes flags the loss sum takes the counters from them and no atomics run.
+constexpr int kTokWaves = 4;                     // tokens (waves) per workgroup
+
+__global__ __launch_bounds__(64 * kTokWaves) void lmh_tokens(RowArgs a, LmhArgs m, int count) {
   const int lane = threadIdx.x & 63;
-  if (t >= m.T) return;
-  const int64_t y = m.ids[t];
-  float acc = 0.0f;
-  if (y >= 0 && y < m.V) {
-    const uint16_t* h = m.hidden + (int64_t)t * m.d;
+  const int ngroups = lmh_groups(m.V);
+  StatCount sc;
+  for (int64_t t0 = (int64_t)blockIdx.x * kTokWaves; t0 < m.T; t0 += (int64_t)gridDim.x * kTokWaves) {
+    const int64_t t = t0 + (threadIdx.x >> 6);
+    if (t >= m.T) break;                         // the whole wave
+    const bool valid = a.mask == nullptr || a.mask[t] != 0;
+    const int64_t y = m.ids[t];
+    const bool ev = valid && y >= 0 && y < m.V;  // uniform over the wave
+    if (!ev) {
+      if (lane == 0) {
+        a.lp_out[t] = valid ? __builtin_nanf("") : 0.0f;
+        a.loss_tok[t] = 0.0f;
+        if (a.flags) a.flags[t] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
+        if (valid) sc.bad += 1;
+        m.w[t] = 0.0f;
+        m.lse2[t] = 0.0f;
+        m.dy[t] = 0.0f;
+        m.ev[t] = 0;
+      }
+      continue;
+    }
+    const TokenIn tin = token_inputs_lane(a, t);
+    constexpr int U = 8;                         // partials per lane in flight
+    const f32x2* p = (const f32x2*)m.part + t * ngroups;
+    float n = -INFINITY, s = 0.0f;
+    for (int q0 = lane; q0 < ngroups; q0 += 64 * U) {
+      f32x2 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + 64 * u;
+        v[u] = p[q < ngroups ? q : lane];        // in bounds: q0 < ngroups, so lane is
+        if (q >= ngroups) v[u] = f32x2{-INFINITY, 0.0f};
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) merge_ns(n, s, v[u].x, v[u].y);
+    }
+    float zy = 0.0f;
+    const uint16_t* h = m.hidden + t * m.d;
     const uint16_t* wr = m.weight + y * m.d;
+#pragma unroll 4
     for (int k = lane * 8; k < m.d; k += 512) {
       const u32x4 hv = *(const u32x4*)(h + k);
       const u32x4 wv = *(const u32x4*)(wr + k);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        acc = __builtin_fmaf(bf16_lo(hv[i]), bf16_lo(wv[i]), acc);
-        acc = __builtin_fmaf(bf16_hi(hv[i]), bf16_hi(wv[i]), acc);
+        zy = __builtin_fmaf(bf16_lo(hv[i]), bf16_lo(wv[i]), zy);
+        zy = __builtin_fmaf(bf16_hi(hv[i]), bf16_hi(wv[i]), zy);
       }
     }
-  }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) m.zy[t] = acc;
-}
-
-// One thread per token: merge the tile partials into lse, then the token math. Writes the
-// per-token outputs and the backward constants; counters are reduced per workgroup.
-__global__ __launch_bounds__(256) void lmh_finish(RowArgs a, LmhArgs m) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  bool band = false, ppo = false, active = false, bad = false;
-  if (t < m.T) {
-    const bool valid = a.mask == nullptr || a.mask[t] != 0;
-    const int64_t y = m.ids[t];
-    const bool good = y >= 0 && y < m.V;
-    float w = 0.0f, l2 = 0.0f;
-    uint8_t ev = 0;
-    if (!valid) {
-      a.lp_out[t] = 0.0f;
-      a.loss_tok[t] = 0.0f;
-      if (a.flags) a.flags[t] = 0;
-    } else if (!good) {
-      a.lp_out[t] = __builtin_nanf("");
-      a.loss_tok[t] = 0.0f;
-      if (a.flags) a.flags[t] = (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID);
-      bad = true;
-    } else {
-      float n = -INFINITY, s = 0.0f;
-      const int ngroups = lmh_groups(m.V);
-      const float* p = m.part + (int64_t)t * ngroups * 2;
-      for (int i = 0; i < ngroups; ++i) merge_ns(n, s, p[2 * i], p[2 * i + 1]);
-      l2 = (n == -INFINITY) ? __builtin_nanf("") : n + log2f(s);
-      const TokenOut o = token_math(a, token_inputs_lane(a, t), m.zy[t], l2);
+    for (int off = 32; off >= 1; off >>= 1) {
+      zy += __shfl_xor(zy, off, 64);
+      const float n2 = __shfl_xor(n, off, 64);
+      const float s2 = __shfl_xor(s, off, 64);
+      merge_ns(n, s, n2, s2);
+    }
+    const float l2 = (n == -INFINITY) ? __builtin_nanf("") : n + log2f(s);
+    if (lane == 0) {
+      const TokenOut o = token_math(a, tin, zy, l2);
       a.lp_out[t] = o.lp;
       a.loss_tok[t] = o.loss;
       if (a.flags) a.flags[t] = o.flags;
-      w = o.w;
-      ev = 1;
-      band = o.flags & DPPO_FLAG_BAND;
-      ppo = o.flags & DPPO_FLAG_PPO;
-      const bool uses_mask = a.rd_mode == DPPO_RD_MASK || a.rd_mode == DPPO_RD_MASK_WEIGHT;
-      active = ppo && (band || !uses_mask);
-    }
-    m.w[t] = w;
-    m.lse2[t] = l2;
-    m.ev[t] = ev;
-  }
-  const int nb = __syncthreads_count(band);
-  const int np = __syncthreads_count(ppo);
-  const int na = __syncthreads_count(active);
-  const int nbad = __syncthreads_count(bad);
-  if (threadIdx.x == 0) {
-    if (nb) atomicAdd(&a.stats[DPPO_STAT_N_BAND], nb);
-    if (np) atomicAdd(&a.stats[DPPO_STAT_N_PPO], np);
-    if (na) atomicAdd(&a.stats[DPPO_STAT_N_ACTIVE], na);
-    if (nbad) atomicAdd(&a.stats[DPPO_STAT_N_BAD], nbad);
-  }
-}
-
-// Full-vocabulary backward without a second product, in two passes.
-// lmh_row_stats, one 256-thread workgroup per token row (looping over rows): merges the
-// row's group partials into lse2, runs the token math (per-token outputs, counters kept per
-// workgroup) and leaves the backward constants w, lse2, dy = w (p_y - 1) (as token_math
-// computes it from z[y]) and ev for the scale pass.
-// lmh_grad_scale turns the stored exponentials into G = w (softmax - onehot) in place, one
-// 16-byte chunk (8 entries) per thread: entry v of group q becomes w 2^(m2_q - lse2) e_v in
-// bf16, the sampled entry dy, and the entries from V up to ldg zeros; a row that is not
-// evaluated (masked, or a bad id) becomes zeros without being read. One chunk per thread
-// and a grid of (chunks per row / 256) x T workgroups is the shape in which a read-write
-// stream moves the most bytes per second on MI355X (as a per-row loop over four chunks per
-// thread it took 1.0 ms at T = 8192, V = 151936).
-constexpr int kGR = 256;
-
-__global__ __launch_bounds__(kGR) void lmh_row_stats(RowArgs a, LmhArgs m) {
-  __shared__ float red[2 * (kGR / 64) + 2];
-  StatCount sc;
-  const int tid = threadIdx.x;
-  const int ngroups = lmh_groups(m.V);
-  for (int64_t row = blockIdx.x; row < m.T; row += gridDim.x) {
-    const bool valid = a.mask == nullptr || uload_u8(a.mask + row) != 0;
-    const int64_t y = uload(m.ids + row);
-    const bool ev = valid && y >= 0 && y < m.V;           // uniform over the workgroup
-    if (ev) {
-      float n = -INFINITY, s = 0.0f;
-      for (int q = tid; q < ngroups; q += kGR) {
-        const float* p = m.part + (row * ngroups + q) * 2;
-        merge_ns(n, s, p[0], p[1]);
-      }
-      block_merge_ns<kGR>(n, s, red);  // once per row: its second barrier orders the reuse
-      const float l2 = (n == -INFINITY) ? __builtin_nanf("") : n + log2f(s);
-      if (tid == 0) {
-        const TokenOut o = token_math(a, token_inputs(a, row), uload(m.zy + row), l2);
-        a.lp_out[row] = o.lp;
-        a.loss_tok[row] = o.loss;
-        if (a.flags) a.flags[row] = o.flags;
-        count_stats(a, o.flags, sc);
-        m.w[row] = o.w;
-        m.lse2[row] = l2;
-        m.dy[row] = o.dy;
-        m.ev[row] = 1;
-      }
-    } else if (tid == 0) {
-      a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
-      a.loss_tok[row] = 0.0f;
-      if (a.flags) a.flags[row] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
-      if (valid) sc.bad += 1;
-      m.w[row] = 0.0f;
-      m.lse2[row] = 0.0f;
-      m.dy[row] = 0.0f;
-      m.ev[row] = 0;
+      count_stats(a, o.flags, sc);
+      m.w[t] = o.w;
+      m.lse2[t] = l2;
+      m.dy[t] = o.dy;
+      m.ev[t] = 1;
     }
   }
-  if (tid == 0) flush_stats(a, sc);
+  if (count && lane == 0) flush_stats(a, sc);
 }
 
+// Full-vocabulary backward without a second product: lmh_grad_scale turns the stored
+// exponentials into G = w (softmax - onehot) in place, one 16-byte chunk (8 entries) per
+// thread: entry v of group q becomes w 2^(m2_q - lse2) e_v in bf16, the sampled entry dy, and
+// the entries from V up to ldg zeros; a row that is not evaluated (masked, or a bad id) becomes
+// zeros without being read. One chunk per thread and a grid of (chunks per row / 256) x T
+// workgroups is the shape in which a read-write stream moves the most bytes per second on
+// MI355X (as a per-row loop over four chunks per thread it took 1.0 ms at T = 8192,
+// V = 151936).
 __global__ __launch_bounds__(256) void lmh_grad_scale(LmhArgs m, int per_row) {
   // per_row workgroups cover a row's chunks; consecutive workgroups walk along a row
   const int64_t row = blockIdx.x / per_row;
@@ -525,29 +483,24 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_bwd_tiles(LmhArgs m) {
   LMH_RUN_ENGINE(m, m0, r0, epi);
 }
 
-hipError_t launch_lmh_zy(const LmhArgs& m, hipStream_t st) {
-  lmh_zy<<<(m.T + 3) / 4, 256, 0, st>>>(m);
-  return hipGetLastError();
-}
-
 hipError_t launch_lmh_fwd_tiles(const LmhArgs& m, hipStream_t st) {
   const dim3 grid((m.T + LMH_BM - 1) / LMH_BM, lmh_tiles(m.n1 - m.n0));
   lmh_fwd_tiles<<<grid, LMH_THREADS, 0, st>>>(m);
   return hipGetLastError();
 }
 
-hipError_t launch_lmh_finish(const RowArgs& a, const LmhArgs& m, hipStream_t st) {
-  lmh_finish<<<(m.T + 255) / 256, 256, 0, st>>>(a, m);
+hipError_t launch_lmh_tokens(const RowArgs& a, const LmhArgs& m, bool count, hipStream_t st) {
+  if (m.T <= 0) return hipSuccess;
+  const int64_t groups = ((int64_t)m.T + kTokWaves - 1) / kTokWaves;
+  // with counter atomics, few workgroups: five atomics each on the same addresses
+  const int64_t most = count ? 256 : 0x7fffffff;
+  lmh_tokens<<<(unsigned)(groups < most ? groups : most), 64 * kTokWaves, 0, st>>>(a, m, count ? 1 : 0);
   return hipGetLastError();
 }
 
-hipError_t launch_lmh_grad_rows(const RowArgs& a, const LmhArgs& m, hipStream_t st) {
+hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st) {
   if (m.ldg % 8 != 0 || m.ldg / 8 > 0x7fffffff) return hipErrorInvalidValue;
   if (m.T <= 0) return hipSuccess;
-  const int grid = m.T < 2048 ? m.T : 2048;
-  lmh_row_stats<<<grid, kGR, 0, st>>>(a, m);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int64_t per_row = (m.ldg / 8 + 255) / 256;
   if (per_row * m.T > 0x7fffffff) return hipErrorInvalidValue;
   lmh_grad_scale<<<(unsigned)(per_row * m.T), 256, 0, st>>>(m, (int)per_row);

@@ -304,3 +304,18 @@ def test_lm_head_autograd_wrapper_returns_the_call_gradients():
     assert torch.equal(h.grad, (3.0 * direct.dhidden).to(torch.bfloat16))
     assert torch.equal(w.grad, (3.0 * direct.dweight).to(torch.bfloat16))
 
+
+
+@pytest.mark.parametrize("T,d,V", [(1, 8, 300), (5, 520, 33000), (67, 1032, 16500)])
+def test_token_pass_edges_and_counters_without_flags(T, d, V):
+    """The token pass (one wave per token, four tokens per workgroup): fewer tokens than a
+    workgroup holds, a remainder, more than 64 x 8 groups' worth of partials (V > 65536 / 2 is
+    one round of its loop, 33000 two loads per lane), d past one wave-wide step. The counters
+    are the same whether they come from the flags or, without flags, from atomics."""
+    wl, res, _ = _run(T, d, V, seed=40 + T, bad_ids=(0,) if T > 1 else ())
+    lp_ref = res.logp.nan_to_num() - 0.1
+    a = P.fused_lm_head_loss_fwd_bwd(wl.hidden, wl.weight, wl.ids, lp_ref, lp_ref, wl.adv, wl.mask)
+    b = P.fused_lm_head_loss_fwd_bwd(wl.hidden, wl.weight, wl.ids, lp_ref, lp_ref, wl.adv, wl.mask,
+                                     want_flags=False)
+    assert torch.equal(a.stats, b.stats) and torch.equal(a.loss, b.loss)
+    assert torch.equal(a.logp.nan_to_num(7.0), b.logp.nan_to_num(7.0))
