@@ -615,6 +615,12 @@ dppo_status fused_lm_head_loss_fwd_bwd(
         g.c = dhidden;
         g.ldc = d;
         g.accumulate = n0 > 0;
+        // the chunk's dweight rows are written only after this product: until then they are
+        // scratch for slices of a long K
+        if (dweight && aligned16(dweight) && aligned16(dhidden)) {
+          g.part = dweight + n0 * d;
+          g.part_floats = kc * d;
+        }
         if ((e = timed([&] { return dppo::launch_lmh_grad_gemm(g, false, true, st); })) != hipSuccess)
           return hip_fail(e, "dhidden product launch");
       }
@@ -648,8 +654,10 @@ dppo_status fused_lm_head_loss_fwd_bwd(
       s = products(0, V);
       if (s != DPPO_OK) return s;
     } else {
-      for (int64_t n0 = 0; grads && n0 < V; n0 += L.chunk) {
-        const int64_t n1 = std::min<int64_t>(V, n0 + L.chunk);
+      const int64_t rows =
+          grads ? dppo::lmh_backward_step(T, d, V, L.chunk, dhidden != nullptr, dweight != nullptr) : V;
+      for (int64_t n0 = 0; grads && n0 < V; n0 += rows) {
+        const int64_t n1 = std::min<int64_t>(V, n0 + rows);
         m.n0 = (int32_t)n0;
         m.n1 = (int32_t)n1;
         if ((e = timed([&] { return dppo::launch_lmh_bwd_tiles(m, st); })) != hipSuccess)

@@ -63,7 +63,10 @@ struct GemmArgs {
   float* c;                // [M, ldc] fp32
   int64_t ldc;
   int32_t accumulate;      // 1: C += A B^T; 0: C = A B^T
+  float* part;             // scratch for partial products over slices of K, or NULL; as the
+  int64_t part_floats;     // launcher needs it ([splits, M, N] contiguous, ldc == N)
   int32_t tiles_m, tiles_n;  // set by the launcher
+  int32_t splits, kper;      // set by the launcher: slices of K, and K per slice
 };
 constexpr int LMH_GBM = 256, LMH_GBN = 256;  // C tile of one workgroup
 
@@ -74,5 +77,13 @@ hipError_t launch_lmh_bwd_tiles(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_zero(float* p, int64_t n, hipStream_t st);  // fill kernel (no memset)
 hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_grad_gemm(const GemmArgs& g, bool a_mn, bool b_mn, hipStream_t st);
+
+// Vocabulary rows per step of the chunked backward: at most `chunk` (the rows of G the
+// workspace holds, a multiple of 256), and the multiple of 256 down to a quarter of it with
+// the shortest estimated total over V rows. A step of the whole chunk can leave the last round
+// of tiles of each kernel nearly empty: at T = 2048, d = 4096 a chunk of 11008 rows is 344 logit
+// tiles for 256 CUs, 8192 rows are 256.
+int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool dhidden,
+                          bool dweight);
 
 }  // namespace dppo

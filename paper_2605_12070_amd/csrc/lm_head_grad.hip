@@ -42,6 +42,7 @@
 // cut the L2 misses of dhidden from 22.4 to 16.4 GB and of dW from 33.1 to 17.3 GB per
 // launch (T = 8192, d = 4096, V = 151936) at the same speed: the products are not bound by
 // L2 misses.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -353,8 +354,11 @@ __device__ __forceinline__ void grouped_tile(int L, int tiles_m, int tiles_n, in
 
 }  // namespace
 
-// C (+)= A B^T over the tile of workgroup blockIdx.x; fp32 C stored non-temporally.
-template <bool AMN, bool BMN>
+// C (+)= A B^T over the tile of workgroup blockIdx.x; fp32 C stored non-temporally. With
+// SPLIT the workgroup takes one slice of K and stores its partial product (cached: the sum
+// kernel reads it next) into slice s of g.part. (As a run-time branch in one kernel the slice
+// arithmetic made the unsliced products 5 % slower.)
+template <bool AMN, bool BMN, bool SPLIT>
 __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
   // one LDS object per slot and operand (a 2-D array is one object: the transposing reads of
   // one slot would then wait for the loads into another); unused ones are not allocated
@@ -369,8 +373,19 @@ __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
     ring.a[i] = as[i];
     ring.b[i] = bs[i];
   }
+  const int nt = g.tiles_m * g.tiles_n;
+  int L = xcd_tile(blockIdx.x, SPLIT ? nt * g.splits : nt);
+  if constexpr (SPLIT) {
+    const int s = L / nt;
+    L -= s * nt;
+    const int64_t k0 = (int64_t)s * g.kper;
+    g.a += AMN ? k0 * g.lda : k0;
+    g.b += BMN ? k0 * g.ldb : k0;
+    g.K = min(g.kper, (int)(g.K - k0));
+    g.c = g.part + (int64_t)s * g.M * g.N;
+  }
   int tm, tn;
-  grouped_tile(xcd_tile(blockIdx.x, g.tiles_m * g.tiles_n), g.tiles_m, g.tiles_n, tm, tn);
+  grouped_tile(L, g.tiles_m, g.tiles_n, tm, tn);
   const int m0 = tm * GBM;
   const int n0 = tn * GBN;
   auto epi = [&](f32x16g (&acc)[GTM][GTN], int wm, int wn) {
@@ -389,27 +404,138 @@ __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
           if (m >= g.M) continue;
           float* p = g.c + (int64_t)m * g.ldc + n;
           float v = acc[mi][ni][r];
-          if (g.accumulate) v += *p;
-          __builtin_nontemporal_store(v, p);
+          if constexpr (SPLIT) {
+            *p = v;
+          } else {
+            if (g.accumulate) v += *p;
+            __builtin_nontemporal_store(v, p);
+          }
         }
       }
   };
   grad_engine<AMN, BMN>(g, m0, n0, ring, epi);
 }
 
-template __global__ void lmh_grad_gemm<false, true>(GemmArgs);
-template __global__ void lmh_grad_gemm<true, true>(GemmArgs);
+// C (+)= the sum of the slices' partial products, in slice order (the same bits every run).
+// One float4 per thread: a stream of splits reads and one write, out of the last-level cache.
+__global__ __launch_bounds__(256) void lmh_sum_slices(const f32x4* part, int64_t n4, int splits,
+                                                      f32x4* c, int accumulate) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 v = part[i];
+#pragma unroll 4
+  for (int s = 1; s < splits; ++s) v += part[(int64_t)s * n4 + i];
+  if (accumulate) v += c[i];
+  __builtin_nontemporal_store(v, c + i);
+}
+
+namespace {
+
+constexpr int kTurn = GS * GBK;     // K of one turn of the LDS ring: a slice is whole turns
+constexpr int kMaxSplits = 128;
+
+// Estimated time of a product in microseconds, splits slices of kper K over cus CUs (one
+// workgroup per CU): the constants are those of the full chip at K in the thousands (a
+// 32-deep stage of every CU's tile 0.86 us) and a tile's fixed part (prologue, epilogue); the
+// slices' sum reads and writes at 4 TB/s and costs a launch.
+double gemm_us(int64_t tiles, int64_t splits, int64_t kper, int64_t mn, int cus) {
+  const double waves = (double)((tiles * splits + cus - 1) / cus);
+  const double stages = (double)((kper + kTurn - 1) / kTurn * GS);
+  double t = waves * (0.86 * stages * (GBK / 32) + 8.0);
+  if (splits > 1) t += 5.0 + (double)(splits + 1) * (double)mn * 4.0 / 4.0e6;
+  return t;
+}
+
+int cu_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    return 256;
+  return cus;
+}
+
+}  // namespace
+
+// The product in splits slices of K where that is estimated faster: with few C tiles and a
+// long K (dhidden of a short batch: K is the vocabulary) most CUs would have no tile at all.
+static void lmh_pick_splits(GemmArgs& g, int cus) {
+  g.splits = 1;
+  g.kper = g.K;
+  if (!g.part || g.ldc != g.N || g.N % 4 != 0) return;
+  const int64_t tiles = (int64_t)((g.M + GBM - 1) / GBM) * ((g.N + GBN - 1) / GBN);
+  const int64_t mn = (int64_t)g.M * g.N;
+  double best = gemm_us(tiles, 1, g.K, mn, cus);
+  const int64_t most = std::min<int64_t>(kMaxSplits, g.part_floats / mn);
+  for (int64_t s = 2; s <= most; ++s) {
+    const int64_t kper = ((g.K + s - 1) / s + kTurn - 1) / kTurn * kTurn;
+    const int64_t used = (g.K + kper - 1) / kper;       // slices that hold any K
+    if (used != s) continue;
+    const double t = gemm_us(tiles, s, kper, mn, cus);
+    if (t < best) {
+      best = t;
+      g.splits = (int32_t)s;
+      g.kper = (int32_t)kper;
+    }
+  }
+}
+
+int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool dhidden, bool dweight) {
+  const int cus = cu_count();
+  const int64_t tm = (T + LMH_BM - 1) / LMH_BM, tn = (d + GBN - 1) / GBN;
+  // one step of c vocabulary rows: the logit tiles, then the two products
+  auto step_us = [&](int64_t c) {
+    const int64_t tv = (c + LMH_BN - 1) / LMH_BN;
+    double t = 15.0 + gemm_us(tm * tv, 1, d, 0, cus);
+    if (dhidden) {
+      GemmArgs g{};
+      g.M = (int32_t)T;
+      g.N = (int32_t)d;
+      g.ldc = d;
+      g.K = (int32_t)c;
+      float scratch;
+      if (dweight) {
+        g.part = &scratch;                       // a stand-in: only its size matters here
+        g.part_floats = c * d;
+      }
+      lmh_pick_splits(g, cus);
+      t += gemm_us(tm * tn, g.splits, g.kper, T * d, cus);
+    }
+    if (dweight) t += gemm_us(tv * tn, 1, T, 0, cus);
+    return t;
+  };
+  int64_t best_c = chunk;
+  double best = 0.0;
+  for (int64_t c = chunk; c >= LMH_BN; c -= LMH_BN) {
+    const int64_t whole = V / c, rest = V % c;
+    const double t = (double)whole * step_us(c) + (rest ? step_us(rest) : 0.0);
+    if (c == chunk || t < best) {
+      best = t;
+      best_c = c;
+    }
+    if (c <= chunk / 4) break;
+  }
+  return best_c;
+}
 
 hipError_t launch_lmh_grad_gemm(const GemmArgs& g0, bool a_mn, bool b_mn, hipStream_t st) {
   GemmArgs g = g0;
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   g.tiles_m = (g.M + GBM - 1) / GBM;
   g.tiles_n = (g.N + GBN - 1) / GBN;
-  const int64_t nt = (int64_t)g.tiles_m * g.tiles_n;
+  lmh_pick_splits(g, cu_count());
+  const int64_t nt = (int64_t)g.tiles_m * g.tiles_n * g.splits;
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
   if (!b_mn) return hipErrorInvalidValue;
-  if (a_mn) lmh_grad_gemm<true, true><<<(unsigned)nt, GTHREADS, 0, st>>>(g);
-  else lmh_grad_gemm<false, true><<<(unsigned)nt, GTHREADS, 0, st>>>(g);
+  auto* fn = a_mn ? (g.splits > 1 ? lmh_grad_gemm<true, true, true> : lmh_grad_gemm<true, true, false>)
+                  : (g.splits > 1 ? lmh_grad_gemm<false, true, true> : lmh_grad_gemm<false, true, false>);
+  fn<<<(unsigned)nt, GTHREADS, 0, st>>>(g);
+  if (g.splits > 1) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t n4 = (int64_t)g.M * g.N / 4;
+    lmh_sum_slices<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>((const f32x4*)g.part, n4, g.splits,
+                                                                (f32x4*)g.c, g.accumulate);
+  }
   return hipGetLastError();
 }
 

@@ -319,3 +319,40 @@ def test_token_pass_edges_and_counters_without_flags(T, d, V):
                                      want_flags=False)
     assert torch.equal(a.stats, b.stats) and torch.equal(a.loss, b.loss)
     assert torch.equal(a.logp.nan_to_num(7.0), b.logp.nan_to_num(7.0))
+
+
+@pytest.mark.parametrize("T,d,V,chunk", [(1, 8, 5000, 0), (130, 72, 9001, 0), (257, 264, 4099, 0),
+                                         (300, 128, 6000, 2048), (513, 520, 20000, 4352)])
+def test_hidden_gradient_in_slices_of_the_vocabulary(T, d, V, chunk):
+    """dhidden of a short batch: a few C tiles and a long K, formed in slices of K whose partial
+    products wait in dweight (one pass, and chunk by chunk with accumulation; the last slice
+    and the last chunk ragged). dweight itself is whole afterwards, and a call without dweight
+    (no scratch, one slice) gives the same dhidden up to the order of its sums."""
+    wl, res, _ = _run(T, d, V, seed=60 + T, vocab_chunk=chunk)
+    L = P._lib.lib()
+    ref = torch.empty_like(res.dhidden)
+    n = P.lm_head_workspace_bytes(T, d, V, chunk)
+    ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+    lp = torch.empty(T, device=DEV)
+    outs = [torch.empty(T, device=DEV), torch.empty(T, device=DEV), torch.empty(1, device=DEV)]
+    stats = torch.empty(5, dtype=torch.int32, device=DEV)
+    p = P._lib.DppoParams(0.5, 2.0, 0.2, 0.2, 3, 1, 1.0, 0, 0.5)
+    lp.copy_(res.logp.nan_to_num())
+    import ctypes as C
+
+    def call(dh, dw):
+        P._lib.check(L.fused_lm_head_loss_fwd_bwd(
+            wl.hidden.data_ptr(), wl.weight.data_ptr(), 1, T, d, V, wl.ids.data_ptr(), lp.data_ptr(),
+            lp.data_ptr(), wl.adv.data_ptr(), wl.mask.data_ptr(), None, C.byref(p), outs[0].data_ptr(),
+            outs[1].data_ptr(), outs[2].data_ptr(), None, stats.data_ptr(), dh.data_ptr(),
+            dw.data_ptr() if dw is not None else None, chunk, ws.data_ptr(), n,
+            torch.cuda.current_stream().cuda_stream), "lm head")
+
+    call(ref, None)
+    both = torch.empty_like(ref)
+    call(both, torch.empty_like(res.dweight))
+    torch.cuda.synchronize()
+    # the same bf16 products summed in fp32 in another order: K 2^-24 of their magnitudes' sum,
+    # which |G| |W| bounds; |G| <= 2 |w| per row with |w| <= 2.4 |A| / n_valid
+    bound = V * 2.0 ** -24 * 4.8 * wl.adv.abs().max() / max(1, int(wl.mask.sum())) * wl.weight.float().abs().max()
+    assert (both - ref).abs().max() <= bound
