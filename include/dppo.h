@@ -431,6 +431,22 @@ dppo_status dppo_ppo_clip_ratio(const int32_t* stats, double* ratio);
 dppo_status dppo_reset_decision(const int32_t* stats, double tau, int32_t patience,
                                 int32_t* streak, double* rho, int32_t* fire);
 
+/*
+ * Backward of the autograd wrappers: a gradient of the loss formed by an earlier call, times
+ * the upstream gradient of the loss, in one pass.
+ *
+ * dppo_scale_dlogits -- out = dlogits * g, both [T, V] of `dtype`, contiguous and 16-byte
+ *   aligned; g is rounded to `dtype` first. With flags (the loss call's flags_out; rd_mode and
+ *   loss_tok are then that call's too) a row that is zero in dlogits because its token is
+ *   masked, bad, clipped or out of band is not read and written as 0 * g. out may be dlogits.
+ * dppo_scale_to_bf16 -- dst = bf16(src * g) for n float32 values; both 16-byte aligned.
+ *   g: device float32 scalar.
+ */
+dppo_status dppo_scale_dlogits(const void* dlogits, int32_t dtype, int64_t T, int64_t V,
+                               const uint8_t* flags, const float* loss_tok, int32_t rd_mode,
+                               const float* g, void* out, void* stream);
+dppo_status dppo_scale_to_bf16(const float* src, int64_t n, const float* g, void* dst, void* stream);
+
 /* Row-kernel policy, a testing and benchmarking hook, two bits. Bit 0: clear = automatic
  * (the register-resident kernel when the row fits, the two-pass streaming kernel
  * otherwise), set = always the streaming kernel. Bit 1: decoupled_ppo_loss_fwd_bwd counts

@@ -592,9 +592,26 @@ class EwmaProxyDevice:
             setattr(self, k, sd[k])
 
 
+def _scalable(d: torch.Tensor, g: torch.Tensor, dtype: torch.dtype) -> bool:
+    """True when the library's scale kernels can form d * g: plain tensors on the current
+    device, outside a differentiated backward (create_graph) and outside vmap or tracing, whose
+    tensors have no data pointer."""
+    if torch.is_grad_enabled() or type(d) is not torch.Tensor or type(g) is not torch.Tensor:
+        return False
+    if (d.dtype != dtype or g.dtype != torch.float32 or g.dim() != 0 or not d.is_cuda
+            or d.device != g.device or d.device.index != torch.cuda.current_device()
+            or not d.is_contiguous()):
+        return False
+    try:
+        return d.data_ptr() % 16 == 0 and g.data_ptr() != 0
+    except RuntimeError:
+        return False
+
+
 class DecoupledPPOLoss(torch.autograd.Function):
     """Autograd wrapper: forward runs the fused kernel (loss and dlogits at once); backward
-    returns grad_output * dlogits (one extra elementwise pass when grad_output != 1)."""
+    returns grad_output * dlogits in one pass, which does not read the rows that the forward's
+    flags say are zero (masked, clipped or out-of-band tokens)."""
 
     @staticmethod
     def forward(ctx, logits, token_ids, logp_mu_old, logp_ref, advantages, loss_mask,
@@ -603,19 +620,45 @@ class DecoupledPPOLoss(torch.autograd.Function):
                                          loss_mask, token_scale, **(kwargs or {}))
         ctx.save_for_backward(res.dlogits)
         ctx.mark_non_differentiable(res.logp, res.stats)
+        # Flags and per-token losses of this call alone; buffers the caller owns (out=) may
+        # hold a later call's by the time of the backward.
+        own = "out" not in (kwargs or {}) and res.flags is not None
+        ctx.rows = (res.flags, res.loss_tok) if own else None
+        ctx.rd_mode = (kwargs or {}).get("rd_mode", "mask_weight")
         return res.loss[0], res.logp, res.stats
 
     @staticmethod
     def backward(ctx, g_loss, g_lp, g_stats):
         (d,) = ctx.saved_tensors
-        return (d * g_loss.to(d.dtype), None, None, None, None, None, None, None)
+        if d.dim() == 2 and d.dtype in (torch.bfloat16, torch.float32) and _scalable(d, g_loss, d.dtype):
+            T, V = d.shape
+            flags, loss_tok = ctx.rows if ctx.rows is not None else (None, None)
+            out = torch.empty_like(d)
+            st = _lib.lib().dppo_scale_dlogits(
+                d.data_ptr(), _dtype_code(d), T, V, flags.data_ptr() if flags is not None else None,
+                loss_tok.data_ptr() if loss_tok is not None else None, RD_MODES[ctx.rd_mode],
+                g_loss.data_ptr(), out.data_ptr(), _stream(d.device))
+            _lib.check(st, "dppo_scale_dlogits")
+        else:
+            out = d * g_loss.to(d.dtype)
+        return (out, None, None, None, None, None, None, None)
 
 
 class FusedLMHeadLoss(torch.autograd.Function):
     """Autograd wrapper of the fused LM head: forward runs fused_lm_head_loss_fwd_bwd (the
     loss and both gradients at once, logits never materialised); backward returns
     grad_output * dL/dhidden and grad_output * dL/dweight in the dtypes of hidden and weight
-    (one extra elementwise pass each)."""
+    (one pass each)."""
+
+    @staticmethod
+    def _scaled(d, g, dtype):
+        if dtype == torch.bfloat16 and _scalable(d, g, torch.float32):
+            out = torch.empty_like(d, dtype=dtype)
+            st = _lib.lib().dppo_scale_to_bf16(d.data_ptr(), d.numel(), g.data_ptr(),
+                                               out.data_ptr(), _stream(d.device))
+            _lib.check(st, "dppo_scale_to_bf16")
+            return out
+        return (d * g).to(dtype)
 
     @staticmethod
     def forward(ctx, hidden, weight, token_ids, logp_mu_old, logp_ref, advantages, loss_mask,
@@ -632,7 +675,7 @@ class FusedLMHeadLoss(torch.autograd.Function):
     def backward(ctx, g_loss, g_lp, g_stats):
         dh, dw = ctx.saved_tensors
         th, tw = ctx.dtypes
-        gh = (dh * g_loss).to(th) if ctx.needs_input_grad[0] else None
-        gw = (dw * g_loss).to(tw) if ctx.needs_input_grad[1] else None
+        gh = FusedLMHeadLoss._scaled(dh, g_loss, th) if ctx.needs_input_grad[0] else None
+        gw = FusedLMHeadLoss._scaled(dw, g_loss, tw) if ctx.needs_input_grad[1] else None
         return (gh, gw, None, None, None, None, None, None, None)
 

@@ -52,6 +52,8 @@ SIGNATURES = {
     "decoupled_ppo_loss_shard_fwd_bwd": (I32, [VP, I32, I64, I64, I64, I64, I64, VP, VP, VP, VP, VP,
                                                VP, VP, VP, C.POINTER(DppoParams), VP, VP, VP, VP,
                                                VP, I64, VP, VP]),
+    "dppo_scale_dlogits": (I32, [VP, I32, I64, I64, VP, VP, I32, VP, VP, VP]),
+    "dppo_scale_to_bf16": (I32, [VP, I64, VP, VP, VP]),
     "dppo_strerror": (C.c_char_p, [I32]),
     "dppo_last_error": (C.c_char_p, []),
     "dppo_abi_version": (I32, []),

@@ -21,7 +21,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libdppo.so")
-SOURCES = ["loss_stage.hip", "lm_head.hip", "lm_head_grad.hip", "ewma.hip", "vocab_shard.hip",
+SOURCES = ["loss_stage.hip", "lm_head.hip", "lm_head_grad.hip", "ewma.hip", "vocab_shard.hip", "grad_scale.hip",
            "abi.hip"]
 ARCH = "gfx950"
 

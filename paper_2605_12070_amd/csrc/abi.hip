@@ -12,6 +12,7 @@
 
 #include "dppo.h"
 #include "ewma.h"
+#include "grad_scale.h"
 #include "lm_head.h"
 #include "vocab_shard.h"
 #include "loss_stage.h"
@@ -811,6 +812,44 @@ dppo_status ewma_proxy_step(void* x_prox, const void* x_new, int32_t dtype, int6
                                               (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "ewma step launch");
   return DPPO_OK;
+}
+
+dppo_status dppo_scale_dlogits(const void* dlogits, int32_t dtype, int64_t T, int64_t V,
+                               const uint8_t* flags, const float* loss_tok, int32_t rd_mode,
+                               const float* g, void* out, void* stream) {
+  dppo_status s = check_matrix(dlogits, dtype, T, V, V, "dlogits");
+  if (s != DPPO_OK) return s;
+  if (!g || (T > 0 && !out)) return fail(DPPO_ERR_INVALID_ARG, "g and out are required");
+  if (flags && !loss_tok) return fail(DPPO_ERR_INVALID_ARG, "loss_tok is required with flags");
+  if (rd_mode < DPPO_RD_NONE || rd_mode > DPPO_RD_MASK_WEIGHT)
+    return fail(DPPO_ERR_INVALID_ARG, "unknown rd_mode %d", (int)rd_mode);
+  if (!aligned16(dlogits) || !aligned16(out))
+    return fail(DPPO_ERR_INVALID_ARG, "dlogits and out must be 16-byte aligned");
+  const int es = esize_of(dtype);
+  if (T > 0 && out != dlogits && overlaps(span_of(dlogits, T, V, V, es), span_of(out, T, V, V, es)))
+    return fail(DPPO_ERR_INVALID_ARG, "out overlaps dlogits without aliasing it exactly");
+  dppo::ScaleRowsArgs a{};
+  a.d = dlogits;
+  a.out = out;
+  a.T = (int32_t)T;
+  a.V = (int32_t)V;
+  a.flags = flags;
+  a.loss_tok = loss_tok;
+  a.uses_band = rd_mode == DPPO_RD_MASK || rd_mode == DPPO_RD_MASK_WEIGHT;
+  a.g = g;
+  const hipError_t e = dppo::launch_scale_rows(a, dtype == DPPO_BF16, (hipStream_t)stream);
+  return e == hipSuccess ? DPPO_OK : hip_fail(e, "dlogits scale launch");
+}
+
+dppo_status dppo_scale_to_bf16(const float* src, int64_t n, const float* g, void* dst, void* stream) {
+  if (n < 0) return fail(DPPO_ERR_INVALID_ARG, "n = %lld < 0", (long long)n);
+  if (!g || (n > 0 && (!src || !dst))) return fail(DPPO_ERR_INVALID_ARG, "src, dst and g are required");
+  if (!aligned16(src) || !aligned16(dst))
+    return fail(DPPO_ERR_INVALID_ARG, "src and dst must be 16-byte aligned");
+  if (n > 0 && overlaps(span_of(src, 1, n, n, 4), span_of(dst, 1, n, n, 2)))
+    return fail(DPPO_ERR_INVALID_ARG, "dst overlaps src");
+  const hipError_t e = dppo::launch_scale_to_bf16(src, dst, n, g, (hipStream_t)stream);
+  return e == hipSuccess ? DPPO_OK : hip_fail(e, "scale launch");
 }
 
 // ------------------------------------------------------------------ vocabulary shards

@@ -723,3 +723,55 @@ def test_short_form_matches_the_full_call():
     assert loss.dim() == 0 and torch.equal(loss.view(1), full.loss)
     assert torch.equal(lp, full.logp) and torch.equal(st, full.stats)
     assert torch.equal(d.view(torch.int16), full.dlogits.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [1, 7, 4096, 4099, 8185])
+@pytest.mark.parametrize("rd_mode", ["mask_weight", "weight"])
+def test_autograd_backward_is_dlogits_times_the_upstream_gradient(dtype, V, rd_mode):
+    """The backward's scale pass (rows at every phase, one or several workgroups per row, rows
+    it does not read) against torch's product of the saved gradient and the upstream one:
+    the same values, NaN rows, bad ids and masked rows included, for finite and infinite g."""
+    T = 67
+    _say("autograd scale", dtype, V, rd_mode)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    z = (2 * torch.randn(T, V, generator=g, device=DEV)).to(dtype)
+    z[3] = float("nan")
+    z[5, 0] = float("inf")
+    z[6] = -float("inf")
+    ids = torch.randint(0, V, (T,), generator=g, device=DEV)
+    ids[9] = V
+    mask = (torch.rand(T, generator=g, device=DEV) > 0.4).to(torch.uint8)
+    mask[3:10] = 1
+    lp = torch.log_softmax(z.float(), dim=1).gather(1, ids.clamp(max=V - 1)[:, None])[:, 0].nan_to_num(-5.0)
+    lp_ref = lp + 0.3 * torch.randn(T, generator=g, device=DEV)
+    lp_mu = lp_ref + 0.6 * torch.randn(T, generator=g, device=DEV)
+    adv = torch.randn(T, generator=g, device=DEV)
+    d = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, rd_mode=rd_mode).dlogits
+    for up in (0.3, -7.0, float("inf")):
+        for kw in (dict(rd_mode=rd_mode), dict(rd_mode=rd_mode, want_flags=False)):
+            zr = z.clone().requires_grad_(True)
+            loss, _, _ = P.DecoupledPPOLoss.apply(zr, ids, lp_mu, lp_ref, adv, mask, None, kw)
+            u = torch.tensor(up, device=DEV)
+            (got,) = torch.autograd.grad(loss, zr, u)
+            exp = d * u.to(dtype)
+            assert torch.equal(got.isnan(), exp.isnan())
+            assert torch.equal(got.nan_to_num(7.0), exp.nan_to_num(7.0))
+
+
+def test_autograd_backward_differentiated_and_batched():
+    """A backward that is itself differentiated (create_graph) or batched (is_grads_batched)
+    still works: it is the product of torch tensors there."""
+    wl = W.make_workload("tiny", device=DEV)
+    _say("autograd create_graph, batched")
+    lp = torch.full((wl.T,), -7.0, device=DEV)
+    z = wl.logits.clone().requires_grad_(True)
+    d = P.decoupled_ppo_loss_fwd_bwd(wl.logits, wl.ids, lp, lp, wl.adv).dlogits
+    loss, _, _ = P.DecoupledPPOLoss.apply(z, wl.ids, lp, lp, wl.adv, None, None, None)
+    u = torch.tensor(2.0, device=DEV, requires_grad=True)
+    (gz,) = torch.autograd.grad(loss, z, u, create_graph=True)
+    (gu,) = torch.autograd.grad(gz.sum(), u, retain_graph=True)
+    assert torch.allclose(gu, d.sum(), rtol=0, atol=1e-5)
+    us = torch.tensor([1.0, 3.0], device=DEV)
+    (gb,) = torch.autograd.grad(loss, z, us, is_grads_batched=True)
+    assert torch.equal(gb[1], 3.0 * d)
