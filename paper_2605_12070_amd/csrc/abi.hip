@@ -271,7 +271,8 @@ const char* dppo_row_kernel_name(int32_t dtype, int64_t V, int64_t ld, int32_t w
   const char* ty = dtype == DPPO_BF16 ? "bf16" : "f32";
   const char* bw = with_dlogits ? "true" : "false";
   if (L.prefix)
-    snprintf(buf, sizeof(buf), "dppo::rows_%s_prefix<%d, %d>", ty, L.threads, L.chunks);
+    snprintf(buf, sizeof(buf), "dppo::rows_%s_prefix%s<%d, %d>", ty, L.phase ? "_phase" : "", L.threads,
+             L.chunks);
   else if (L.phase && !with_dlogits)
     snprintf(buf, sizeof(buf), "dppo::rows_bf16_fwd_phase<%d, %d>", L.threads, L.chunks);
   else if (L.phase && L.two_buffers)
@@ -286,7 +287,7 @@ const char* dppo_row_kernel_name(int32_t dtype, int64_t V, int64_t ld, int32_t w
     snprintf(buf, sizeof(buf), "dppo::rows_%s_resident<%d, %d, %s>", ty, L.threads, L.chunks, bw);
   else
     snprintf(buf, sizeof(buf), "dppo::rows_stream<%s, %d, %s, %s>",
-             dtype == DPPO_BF16 ? "unsigned short" : "float", L.threads, bw, aligned ? "true" : "false");
+             dtype == DPPO_BF16 ? "unsigned short" : "float", L.threads, bw, L.aligned ? "true" : "false");
   return buf;
 }
 
@@ -366,7 +367,7 @@ dppo_status logprob_fwd(const void* logits, int32_t dtype, int64_t T, int64_t V,
   const int es = esize_of(dtype);
   const bool aligned = aligned16(logits) && ((ld * es) % 16 == 0);
   const dppo::RowLaunch L = dppo::select_row_kernel(dtype, V, aligned, false, g_path_policy,
-                                                    ((uintptr_t)logits & 1) == 0);
+                                                    ((uintptr_t)logits & (uintptr_t)(es - 1)) == 0);
   dppo::RowArgsV a{};
   a.logits = logits;
   a.ld = ld;
@@ -398,12 +399,13 @@ dppo_status logprob_fwd_versioned(const void* const* logits, int32_t K, int32_t 
     return fail(DPPO_ERR_INVALID_ARG, "version_ids, token_ids and logp_out are required");
   const int es = esize_of(dtype);
   bool aligned = (ld * es) % 16 == 0;
-  bool even = true;
+  // the kernels take each row's phase from its own version's matrix
+  bool entry_aligned = true;
   for (int v = 0; v < K; ++v) {
     aligned = aligned && aligned16(logits[v]);
-    even = even && ((uintptr_t)logits[v] & 1) == 0;
+    entry_aligned = entry_aligned && ((uintptr_t)logits[v] & (uintptr_t)(es - 1)) == 0;
   }
-  dppo::RowLaunch L = dppo::select_row_kernel(dtype, V, aligned, false, g_path_policy, even);
+  dppo::RowLaunch L = dppo::select_row_kernel(dtype, V, aligned, false, g_path_policy, entry_aligned);
   // Rows gathered from several versions' logits want every slot of the device: at
   // 1024 x 19 (bf16, V = 151936, 4 versions) 32 of 32 slots took 0.753-0.757 ms against
   // 0.762-0.768 ms with the 30 that suit one matrix (same-box sweep).
@@ -450,9 +452,9 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
                          (!dlogits || (aligned16(dlogits) && (ld_dlogits * es) % 16 == 0));
     // rows with a phase: dlogits row t must start at logits row t's offset within 16 bytes
     const bool phase_ok =
-        ((uintptr_t)logits & 1) == 0 &&
+        ((uintptr_t)logits & (uintptr_t)(es - 1)) == 0 &&
         (!dlogits || ((((uintptr_t)dlogits - (uintptr_t)logits) & 15) == 0 &&
-                      (ld_dlogits - ld) % 8 == 0));
+                      ((ld_dlogits - ld) * es) % 16 == 0));
     L = dppo::select_row_kernel(dtype, V, aligned, dlogits != nullptr, g_path_policy, phase_ok);
   }
   // Count mode: a persistent fp32 resident row kernel on a batch short enough for every

@@ -75,6 +75,7 @@ struct RowLaunch {
   bool two_buffers = false; // resident backward kernel with two row buffers
   bool prefix = false;       // backward kernel with a resident prefix and a streamed tail
   bool phase = false;        // bf16 resident kernel for rows with a phase (rows_bf16_*phase*)
+  bool aligned = false;      // streaming kernel: its last template argument
   bool counts = false;       // the kernel supports count mode (RowArgs::count_mode)
   int fill = 27;             // persistent grids: workgroups launched per 32 resident slots
   int stagger = 2;           // RowArgs::stagger for the kernels that stagger their starts
@@ -87,9 +88,9 @@ constexpr int kPrefixKeepF32 = 9;
 // and the bf16 prefix kernel, beside its 76 KB shift table
 constexpr int kPrefixKeepBf16 = 5;
 
-// aligned: the rows (and dlogits rows) start on 16-byte boundaries. phase_ok: bf16 rows that
-// start anywhere (2-byte aligned), with dlogits (if any) at the logits' phase on every row;
-// rows that are not aligned or not a whole number of chunks then use the phase kernels.
+// aligned: the rows (and dlogits rows) start on 16-byte boundaries. phase_ok: rows that start
+// on any entry's own boundary, with dlogits (if any) at the logits' phase on every row (the
+// same offset within 16 bytes); without it only the streaming kernel takes them.
 RowLaunch select_row_kernel(int32_t dtype, int64_t V, bool aligned, bool bwd, int force,
                             bool phase_ok = false);
 void launch_prep_stats(const uint8_t* mask, int64_t T, int32_t* stats, hipStream_t st);

@@ -8,10 +8,11 @@
 // logits in the same registers as fp16 pairs, so the backward sweep reads nothing from
 // memory and writes dlogits once with 16-byte non-temporal stores. bf16 rows that start
 // anywhere or end in a partial chunk run in the same kernels with the neighbouring entries
-// masked (the phase kernels). Rows longer than the register budget keep a resident prefix
-// and read only the rest twice (the prefix kernels); what is left (fp32 rows off a 16-byte
-// boundary, forward calls on rows past the budget) uses a streaming kernel that reads the
-// row twice.
+// masked (the phase kernels); the fp32 kernels take rows that start and end anywhere as their
+// whole chunks plus a few single entries. Rows longer than the register budget keep a
+// resident prefix and read only the rest twice (the prefix kernels); what is left (forward
+// calls on rows past the budget, dlogits at another offset within 16 bytes than the logits)
+// uses a streaming kernel that reads the row once per pass.
 #include "dppo.h"
 #include "dppo_device.h"
 #include "loss_stage.h"
@@ -110,39 +111,39 @@ __device__ float call_scale(const RowArgs& a) {
   return a.loss_scale / (float)(n > 1 ? n : 1);
 }
 
+// A row of V entries cut into its whole aligned 16-byte chunks and the entries before and after
+// them (fewer than a chunk at each end): nfull chunks from entry `lead` on, nedge single
+// entries, the i-th of them entry<E>(i).
+struct RowSplit {
+  int lead, nfull, nedge;
+  template <int E>
+  __device__ __forceinline__ int entry(int i) const { return i < lead ? i : nfull * E + i; }
+};
+template <typename Tin>
+__device__ __forceinline__ RowSplit split_row(const Tin* row, int V) {
+  constexpr int E = 16 / (int)sizeof(Tin);
+  RowSplit sp;
+  sp.lead = min(V, (int)((0u - (uint32_t)(uintptr_t)row) & 15u) / (int)sizeof(Tin));
+  sp.nfull = (V - sp.lead) / E;
+  sp.nedge = V - sp.nfull * E;
+  return sp;
+}
+
+// Zeros for a gradient row of V entries at any alignment: 16-byte stores over the whole chunks
+// inside it, single entries before and after them.
+template <typename Tin, int NT>
+__device__ void zero_row(Tin* d, int V) {
+  constexpr int E = 16 / (int)sizeof(Tin);
+  const RowSplit sp = split_row(d, V);
+  const u32x4 z = {0u, 0u, 0u, 0u};
+  for (int i = threadIdx.x; i < sp.nfull; i += NT) __builtin_nontemporal_store(z, (u32x4*)(d + sp.lead) + i);
+  if ((int)threadIdx.x < sp.nedge) d[sp.entry<E>(threadIdx.x)] = (Tin)0;
+}
+
 // Rows that are not evaluated (loss mask 0, or a bad token id on a valid row).
 template <typename Tin, int NT>
 __device__ void skip_row(const RowArgs& a, int64_t row, bool valid, StatCount& sc) {
-  if (a.dlogits) {
-    Tin* d = (Tin*)a.dlogits + row * a.ldd;
-    for (int v = threadIdx.x; v < a.V; v += NT) d[v] = (Tin)0;
-  }
-  if (threadIdx.x == 0) {
-    a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
-    a.loss_tok[row] = 0.0f;
-    if (a.flags) a.flags[row] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
-    if (valid) sc.bad += 1;
-  }
-}
-
-// Zero dlogits row for the register-resident paths: NC 16-byte buffer stores per thread
-// (stores past the row are dropped by the buffer range check) plus a ragged tail.
-template <int NT, int NC, int ES>
-__device__ void skip_row_resident(const RowArgs& a, int64_t row, bool valid, StatCount& sc) {
-  if (a.dlogits) {
-    constexpr int E = 16 / ES;
-    char* d = (char*)a.dlogits + row * a.ldd * ES;
-    const __amdgpu_buffer_rsrc_t rd = row_rsrc(d, a.V * ES);
-    const int nfull = a.V / E;
-    const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (c * NT + (int)threadIdx.x < nfull) buf_store16_nt(z, rd, threadIdx.x * 16, c * NT * 16);
-    for (int e = nfull * E + threadIdx.x; e < a.V; e += NT) {
-      if (ES == 2) ((uint16_t*)d)[e] = 0;
-      else ((float*)d)[e] = 0.0f;
-    }
-  }
+  if (a.dlogits) zero_row<Tin, NT>((Tin*)a.dlogits + row * a.ldd, a.V);
   if (threadIdx.x == 0) {
     a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
     a.loss_tok[row] = 0.0f;
@@ -667,7 +668,11 @@ __global__ __launch_bounds__(NT) void rows_bf16_fwd_phase(RowArgsV a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Register-resident row kernel, fp32 logits (4 per 16-byte chunk; exps stored as fp32).
+// Register-resident row kernel, fp32 logits (4 per 16-byte chunk; exps stored as fp32). Rows
+// may start and end anywhere (RowSplit): the whole chunks go through the registers, an entry
+// at an end through one register of its thread. HBM-bound at any offset: T = 4096, V = 50257
+// contiguous took 0.97 ms in the streaming kernel these rows used before (every row read
+// twice, 4 bytes per lane) and takes 0.33 ms here.
 // ---------------------------------------------------------------------------------------
 template <int NT, int NC, bool BWD>
 __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
@@ -681,7 +686,6 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
   auto one = [&](const int64_t row) {
     const int tid = threadIdx.x;
     const int V = a.V;
-    const int nfull = V >> 2;
     // Every scalar load of the row is issued before the first branch on any of them (a
     // branch on a loaded value waits for all scalar loads in flight), so they share one
     // round trip; the token inputs are used after the merge. With one row per workgroup
@@ -695,14 +699,20 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
     const bool valid = ((mword >> (8u * (uint32_t)(((uintptr_t)a.mask + (uintptr_t)row) & 3u))) & 0xffu) != 0;
     const bool good = (y >= 0) && (y < V) && version_ok(a, row);
     if (loss_mode && !(valid && good)) {
-      skip_row_resident<NT, NC, 4>(a, row, valid, sc);
+      skip_row<float, NT>(a, row, valid, sc);
       return;
     }
     const float* zrow = row_ptr<float>(a, row);
     float zy = 0.0f;
     if (tid == 0 && good) zy = zrow[y];
 
-    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow, V * 4);
+    const RowSplit sp = split_row(zrow, V);
+    const int nfull = sp.nfull;
+    const bool edge = tid < sp.nedge;
+    const int ei = sp.entry<4>(tid);
+    float xe = -INFINITY;
+    if (edge) xe = zrow[ei];
+    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow + sp.lead, nfull * 16);
     const int voff = tid * 16;
     float r[NC][4];
 #pragma unroll
@@ -717,22 +727,7 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
         r[c][0] = r[c][1] = r[c][2] = r[c][3] = -INFINITY;
       }
     }
-    const int tail_slot = nfull / NT;
-    const bool tail_owner = (V & 3) != 0 && tid == nfull % NT;
-    if (tail_owner) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c == tail_slot) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int e = nfull * 4 + j;
-            if (e < V) r[c][j] = zrow[e];
-          }
-        }
-      }
-    }
-
-    float m = -INFINITY;
+    float m = xe;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       m = max3(m, r[c][0], r[c][1]);
@@ -740,7 +735,8 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
     }
     const float n_shift = (m == -INFINITY) ? 0.0f : m * kLog2e;
     const float nb = -n_shift;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    const float ee = exp2_hw(__builtin_fmaf(xe, kLog2e, nb));
+    float s0 = ee, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       float e[4];
@@ -765,10 +761,11 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
     const float dy = bc.dy;
     const float f = row_factor(w, n_mine, bc.lse2);
     float* drow = (float*)a.dlogits + row * a.ldd;
-    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow, V * 4);
-    const int cy = (int)(y >> 2);
-    const int my_slot = (cy % NT == tid) ? cy / NT : -1;
-    const int jy = (int)(y & 3);
+    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow + sp.lead, nfull * 16);
+    const int yb = (int)y - sp.lead;         // the sampled entry within the whole chunks
+    const int cy = yb >> 2;
+    const int my_slot = (yb >= 0 && cy % NT == tid) ? cy / NT : -1;
+    const int jy = yb & 3;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int idx = c * NT + tid;
@@ -783,14 +780,9 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
         const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]),
                          __float_as_uint(o[3])};
         buf_store16_nt(v, rd, voff, c * NT * 16);
-      } else if (tail_owner && c == tail_slot) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int e = nfull * 4 + j;
-          if (e < V) drow[e] = o[j];
-        }
       }
     }
+    if (edge) drow[ei] = (ei == y) ? dy : ee * f;
   };
   for (int64_t row = blockIdx.x; row < a.T; row += gridDim.x) one(row);
   // in count mode the counters come from the flags (loss_sum)
@@ -801,7 +793,13 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
 // Streaming row kernel: any V, any alignment. Pass A reads the row once for (n, s); pass
 // B reads it again to write dlogits. Element e of the row is read and written by the same
 // thread, so dlogits may alias the logits.
+// A row's whole aligned 16-byte chunks are read and written as such, at any offset of the row
+// (RowSplit), the entries at its ends one by one; dlogits must then have the logits' phase on
+// every row. rows_stream_entries takes the rest, one entry per access. kStreamU chunks per
+// thread are in flight: forward rows of V = 262144 bf16 (T = 4096) 481 us with one, 380 us.
 // ---------------------------------------------------------------------------------------
+constexpr int kStreamU = 4;
+
 template <typename Tin>
 __device__ __forceinline__ float load_elem(const Tin* p, int64_t i);
 template <>
@@ -819,60 +817,12 @@ __device__ __forceinline__ void store_elem<uint16_t>(uint16_t* p, int64_t i, flo
   p[i] = to_bf16(x);
 }
 
-// E elements per chunk: 16-byte vectors when VEC, single elements otherwise.
-template <typename Tin, bool VEC>
-struct Chunk {
-  static constexpr int E = VEC ? (int)(16 / sizeof(Tin)) : 1;
-  __device__ static void load(const Tin* row, int idx, int V, float (&x)[E]) {
-    if constexpr (VEC) {
-      if ((idx + 1) * E <= V) {
-        const u32x4 v = ((const u32x4*)row)[idx];
-        if constexpr (sizeof(Tin) == 2) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            x[2 * k] = bf16_lo(v[k]);
-            x[2 * k + 1] = bf16_hi(v[k]);
-          }
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) x[k] = __uint_as_float(v[k]);
-        }
-        return;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int e = idx * E + j;
-      x[j] = e < V ? load_elem<Tin>(row, e) : -INFINITY;
-    }
-  }
-  __device__ static void store(Tin* row, int idx, int V, const float (&o)[E]) {
-    if constexpr (VEC) {
-      if ((idx + 1) * E <= V) {
-        u32x4 v;
-        if constexpr (sizeof(Tin) == 2) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = pack_bf16(o[2 * k], o[2 * k + 1]);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(o[k]);
-        }
-        __builtin_nontemporal_store(v, ((u32x4*)row) + idx);
-        return;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int e = idx * E + j;
-      if (e < V) store_elem<Tin>(row, e, o[j]);
-    }
-  }
-};
+enum StreamRows { kRowsAligned, kRowsAnywhere, kRowsByEntry };
 
-template <typename Tin, int NT, bool BWD, bool VEC>
-__global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
-  using C = Chunk<Tin, VEC>;
-  constexpr int E = C::E;
+template <typename Tin, int NT, bool BWD, StreamRows ROWS>
+__device__ __forceinline__ void stream_rows(const RowArgsOf<BWD>& a) {
+  constexpr int E = 16 / (int)sizeof(Tin);
+  constexpr int U = kStreamU;
   __shared__ float red[2 * (NT / 64) + 2];
   __shared__ Bcast bc;
   StatCount sc;
@@ -883,7 +833,6 @@ __global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
   auto one = [&](const int64_t row) {
     const int tid = threadIdx.x;
     const int V = a.V;
-    const int nchunk = (V + E - 1) / E;
     // the row's scalar loads, issued before the first branch on any of them (the token
     // inputs are used after the merge)
     const uint32_t mword =
@@ -902,19 +851,57 @@ __global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
     float zy = 0.0f;
     if (tid == 0 && good) zy = load_elem<Tin>(zrow, y);
 
+    // f(e0, x) for this thread's share of the row, x the entries from e0 on: E of them for a
+    // whole chunk, one otherwise
+    auto each = [&](auto&& f) {
+      if constexpr (ROWS != kRowsByEntry) {
+        const RowSplit sp = ROWS == kRowsAligned ? RowSplit{0, V / E, V % E} : split_row(zrow, V);
+        const u32x4* zc = (const u32x4*)(zrow + sp.lead);
+        auto chunk = [&](const u32x4& v, int i) {
+          float x[E];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if constexpr (sizeof(Tin) == 2) {
+              x[2 * k] = bf16_lo(v[k]);
+              x[2 * k + 1] = bf16_hi(v[k]);
+            } else {
+              x[k] = __uint_as_float(v[k]);
+            }
+          }
+          f(sp.lead + i * E, x);
+        };
+        int i = tid;
+        for (; i < sp.nfull - (U - 1) * NT; i += U * NT) {
+          u32x4 v[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) v[u] = zc[i + u * NT];
+#pragma unroll
+          for (int u = 0; u < U; ++u) chunk(v[u], i + u * NT);
+        }
+        for (; i < sp.nfull; i += NT) chunk(zc[i], i);
+        if (tid < sp.nedge) {
+          const float x[1] = {load_elem<Tin>(zrow, sp.entry<E>(tid))};
+          f(sp.entry<E>(tid), x);
+        }
+      } else {
+        for (int e = tid; e < V; e += NT) {
+          const float x[1] = {load_elem<Tin>(zrow, e)};
+          f(e, x);
+        }
+      }
+    };
+
     float n = -INFINITY, s = 0.0f;
-    for (int idx = tid; idx < nchunk; idx += NT) {
-      float x[E];
-      C::load(zrow, idx, V, x);
+    each([&]<int N>(int, const float (&x)[N]) {
       float m = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < E; ++j) m = fmaxf(m, x[j]);
+      for (int j = 0; j < N; ++j) m = fmaxf(m, x[j]);
       const float ns = (m == -INFINITY) ? 0.0f : m * kLog2e;
       float cs = 0.0f;
 #pragma unroll
-      for (int j = 0; j < E; ++j) cs += exp2_hw(__builtin_fmaf(x[j], kLog2e, -ns));
+      for (int j = 0; j < N; ++j) cs += exp2_hw(__builtin_fmaf(x[j], kLog2e, -ns));
       merge_ns(n, s, (m == -INFINITY) ? -INFINITY : ns, cs);
-    }
+    });
     block_merge_ns<NT>(n, s, red);
     const float lse2 = (n == -INFINITY) ? __builtin_nanf("") : n + log2f(s);
 
@@ -925,20 +912,37 @@ __global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
     const float dy = bc.dy;
     const float nl = -bc.lse2;
     Tin* drow = (Tin*)a.dlogits + row * a.ldd;
-    for (int idx = tid; idx < nchunk; idx += NT) {
-      float x[E];
-      C::load(zrow, idx, V, x);
-      float o[E];
+    each([&]<int N>(int e0, const float (&x)[N]) {
+      float o[N];
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
+      for (int j = 0; j < N; ++j) {
         o[j] = w * exp2_hw(__builtin_fmaf(x[j], kLog2e, nl));
-        if ((int64_t)idx * E + j == y) o[j] = dy;
+        if ((int64_t)e0 + j == y) o[j] = dy;
       }
-      C::store(drow, idx, V, o);
-    }
+      if constexpr (N == 1) {
+        store_elem<Tin>(drow, e0, o[0]);
+      } else {
+        u32x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (sizeof(Tin) == 2) v[k] = pack_bf16(o[2 * k], o[2 * k + 1]);
+          else v[k] = __float_as_uint(o[k]);
+        }
+        __builtin_nontemporal_store(v, (u32x4*)(drow + e0));
+      }
+    });
   };
   for (int64_t row = blockIdx.x; row < a.T; row += gridDim.x) one(row);
   if (threadIdx.x == 0) flush_stats(a, sc);
+}
+
+template <typename Tin, int NT, bool BWD, bool ALIGNED>
+__global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
+  stream_rows<Tin, NT, BWD, ALIGNED ? kRowsAligned : kRowsAnywhere>(a);
+}
+template <typename Tin, int NT, bool BWD>
+__global__ __launch_bounds__(NT) void rows_stream_entries(RowArgsOf<BWD> a) {
+  stream_rows<Tin, NT, BWD, kRowsByEntry>(a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -954,27 +958,8 @@ __global__ __launch_bounds__(NT) void rows_stream(RowArgsOf<BWD> a) {
 // sum) partial, then loads the resident chunks and gives them one shift per thread, as the
 // resident kernel does. Pass B scales the resident exponentials into dlogits, then takes the
 // tail from LDS or reads it again. Element e of the row is read and written by the same
-// thread, so dlogits may alias the logits.
+// thread, so dlogits may alias the logits. Rows may start and end anywhere (RowSplit).
 // ---------------------------------------------------------------------------------------
-template <typename Tin, int NT>
-__device__ void skip_row_long(const RowArgs& a, int64_t row, bool valid, StatCount& sc) {
-  using C = Chunk<Tin, true>;
-  if (a.dlogits) {
-    Tin* d = (Tin*)a.dlogits + row * a.ldd;
-    const int nchunk = (a.V + C::E - 1) / C::E;
-    float z[C::E];
-#pragma unroll
-    for (int j = 0; j < C::E; ++j) z[j] = 0.0f;
-    for (int idx = threadIdx.x; idx < nchunk; idx += NT) C::store(d, idx, a.V, z);
-  }
-  if (threadIdx.x == 0) {
-    a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
-    a.loss_tok[row] = 0.0f;
-    if (a.flags) a.flags[row] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
-    if (valid) sc.bad += 1;
-  }
-}
-
 template <int NT, int NC>
 __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
   constexpr int P = NT * NC;              // resident chunks of a row
@@ -997,7 +982,6 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
   for (int64_t row = blockIdx.x; row < a.T; row += gridDim.x) {
     const int tid = threadIdx.x;
     const int V = a.V;
-    const int nfull = V >> 2;             // whole 16-byte chunks, > P by the selection
     const bool valid = a.mask == nullptr || uload_u8(a.mask + row) != 0;
     const int64_t y = uload(a.ids + row);
     // issued with the row's other scalar loads, before the first branch on them; used after
@@ -1005,17 +989,20 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
     const TokenIn tin = token_inputs(a, row, scale);
     const bool good = (y >= 0) && (y < V);
     if (!(valid && good)) {               // uniform
-      skip_row_long<float, NT>(a, row, valid, sc);
+      skip_row<float, NT>(a, row, valid, sc);
       continue;
     }
     const float* zrow = (const float*)a.logits + row * a.ld;
     float zy = 0.0f;
     if (tid == 0) zy = zrow[y];
-    // Whole chunks through a resource over the row: a chunk past the end (offset kOff)
-    // loads zeros, replaced by -inf below. The V % 4 last elements belong to one thread.
-    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow, nfull * 16);
+    // Whole chunks through a resource over them: a chunk past the end (offset kOff) loads
+    // zeros, replaced by -inf below. An entry at an end belongs to one thread.
+    const RowSplit sp = split_row(zrow, V);
+    const int nfull = sp.nfull;           // P or more, by the selection
+    const bool edge = tid < sp.nedge;
+    const int ei = sp.entry<4>(tid);
+    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow + sp.lead, nfull * 16);
     constexpr int kOff = 0x7fffff00;
-    const bool rag_owner = (V & 3) != 0 && tid == nfull % NT;
     // pass A, tail first, so that its registers and the resident chunks are never live
     // together
     float nt = -INFINITY, st = 0.0f;
@@ -1046,12 +1033,10 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
         merge_ns(nt, st, (m == -INFINITY) ? -INFINITY : ns, cs);
       }
     }
-    if (rag_owner) {
-      for (int e = nfull * 4; e < V; ++e) {
-        const float x = zrow[e];
-        const float ns = (x == -INFINITY) ? 0.0f : x * kLog2e;
-        merge_ns(nt, st, (x == -INFINITY) ? -INFINITY : ns, exp2_hw(__builtin_fmaf(x, kLog2e, -ns)));
-      }
+    if (edge) {
+      const float x = zrow[ei];
+      const float ns = (x == -INFINITY) ? 0.0f : x * kLog2e;
+      merge_ns(nt, st, (x == -INFINITY) ? -INFINITY : ns, exp2_hw(__builtin_fmaf(x, kLog2e, -ns)));
     }
     // pass A, resident chunks: one shift per thread, exponentials in place
     float r[NC][4];
@@ -1089,11 +1074,12 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
     const float l2 = bc.lse2;
     const float f = row_factor(w, n_mine, l2);
     float* drow = (float*)a.dlogits + row * a.ldd;
-    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow, nfull * 16);
+    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow + sp.lead, nfull * 16);
     // pass B, resident chunks (the sampled entry: the thread that holds it)
-    const int cy = (int)(y >> 2);
-    const int jy = (int)(y & 3);
-    const int my_slot = (cy < P && cy % NT == tid) ? cy / NT : -1;
+    const int yb = (int)y - sp.lead;       // the sampled entry within the whole chunks
+    const int cy = yb >> 2;
+    const int jy = yb & 3;
+    const int my_slot = (yb >= 0 && cy < P && cy % NT == tid) ? cy / NT : -1;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       float o[4];
@@ -1126,10 +1112,7 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
         buf_store16_nt(ov, rd, idx < nfull ? idx * 16 : kOff, 0);
       }
     }
-    if (rag_owner) {
-      for (int e = nfull * 4; e < V; ++e)
-        drow[e] = (e == y) ? dy : w * exp2_hw(__builtin_fmaf(zrow[e], kLog2e, -l2));
-    }
+    if (edge) drow[ei] = (ei == y) ? dy : w * exp2_hw(__builtin_fmaf(zrow[ei], kLog2e, -l2));
   }
   if (threadIdx.x == 0) flush_stats(a, sc);
 }
@@ -1143,10 +1126,13 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
 // read, V - 8 NT NC read again, V written, against 2 V read and V written by the streaming
 // kernel. Persistent, one workgroup per row at a time; pass A streams the tail first, so
 // that its registers and the resident chunks are never live together. Element e of the row
-// is read and written by the same thread, so dlogits may alias the logits.
+// is read and written by the same thread, so dlogits may alias the logits. Rows may start and
+// end anywhere (RowSplit).
 // ---------------------------------------------------------------------------------------
-template <int NT, int NC>
-__global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
+// PH: rows that start anywhere. (The fp32 kernel takes them without a variant of its own; here
+// the run-time offset cost the aligned rows 2 %.)
+template <int NT, int NC, bool PH>
+__device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
   constexpr int P = NT * NC;              // resident chunks of a row
   constexpr int U = 4;                    // tail chunks per thread in flight
   // the first KS of each thread's tail chunks also wait in LDS between the passes (each
@@ -1162,7 +1148,6 @@ __global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
   for (int64_t row = blockIdx.x; row < a.T; row += gridDim.x) {
     const int tid = threadIdx.x;
     const int V = a.V;
-    const int nfull = V >> 3;             // whole 16-byte chunks, >= P by the selection
     const bool valid = a.mask == nullptr || uload_u8(a.mask + row) != 0;
     const int64_t y = uload(a.ids + row);
     // issued with the row's other scalar loads, before the first branch on them; used after
@@ -1170,17 +1155,20 @@ __global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
     const TokenIn tin = token_inputs(a, row, scale);
     const bool good = (y >= 0) && (y < V);
     if (!(valid && good)) {               // uniform
-      skip_row_long<uint16_t, NT>(a, row, valid, sc);
+      skip_row<uint16_t, NT>(a, row, valid, sc);
       continue;
     }
     const uint16_t* zrow = (const uint16_t*)a.logits + row * a.ld;
     float zy = 0.0f;
     if (tid == 0) zy = bf16_to_f32(zrow[y]);
-    // Whole chunks through a resource over the row: a chunk past the end (offset kOff)
-    // loads zeros, replaced by -inf below. The V % 8 last elements belong to one thread.
-    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow, nfull * 16);
+    // Whole chunks through a resource over them: a chunk past the end (offset kOff) loads
+    // zeros, replaced by -inf below. An entry at an end belongs to one thread.
+    const RowSplit sp = PH ? split_row(zrow, V) : RowSplit{0, V >> 3, V & 7};
+    const int nfull = sp.nfull;           // P or more, by the selection
+    const bool edge = tid < sp.nedge;
+    const int ei = sp.entry<8>(tid);
+    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow + sp.lead, nfull * 16);
     constexpr int kOff = 0x7fffff00;
-    const bool rag_owner = (V & 7) != 0 && tid == nfull % NT;
     // pass A, tail: general (max, sum) partials per chunk
     float nt = -INFINITY, st = 0.0f;
     for (int i0 = P + tid, s0 = 0; i0 < nfull; i0 += U * NT, s0 += U) {
@@ -1213,12 +1201,10 @@ __global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
         merge_ns(nt, st, (m == -INFINITY) ? -INFINITY : ns, cs);
       }
     }
-    if (rag_owner) {
-      for (int e = nfull * 8; e < V; ++e) {
-        const float x = bf16_to_f32(zrow[e]);
-        const float ns = (x == -INFINITY) ? 0.0f : x * kLog2e;
-        merge_ns(nt, st, (x == -INFINITY) ? -INFINITY : ns, exp2_hw(__builtin_fmaf(x, kLog2e, -ns)));
-      }
+    if (edge) {
+      const float x = bf16_to_f32(zrow[ei]);
+      const float ns = (x == -INFINITY) ? 0.0f : x * kLog2e;
+      merge_ns(nt, st, (x == -INFINITY) ? -INFINITY : ns, exp2_hw(__builtin_fmaf(x, kLog2e, -ns)));
     }
     // pass A, resident chunks: shift n_c = ceil(L max(chunk)), fp16 exponentials in place
     uint32_t r[NC][4];
@@ -1259,12 +1245,13 @@ __global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
     const float dy = bc.dy;
     const float l2 = bc.lse2;
     uint16_t* drow = (uint16_t*)a.dlogits + row * a.ldd;
-    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow, nfull * 16);
+    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow + sp.lead, nfull * 16);
     // pass B, resident chunks: w 2^(n_c - lse2) e (the sampled entry: the thread that holds
     // it); a NaN lse (non-finite row) makes every element NaN
-    const int cy = (int)(y >> 3);
-    const int jy = (int)(y & 7);
-    const int my_slot = (cy < P && cy % NT == tid) ? cy / NT : -1;
+    const int yb = (int)y - sp.lead;
+    const int cy = yb >> 3;
+    const int jy = yb & 7;
+    const int my_slot = (yb >= 0 && cy < P && cy % NT == tid) ? cy / NT : -1;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const float ncv = nch[c][tid];
@@ -1312,12 +1299,19 @@ __global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
         buf_store16_nt(ov, rd, idx < nfull ? idx * 16 : kOff, 0);
       }
     }
-    if (rag_owner) {
-      for (int e = nfull * 8; e < V; ++e)
-        drow[e] = to_bf16((e == y) ? dy : w * exp2_hw(__builtin_fmaf(bf16_to_f32(zrow[e]), kLog2e, -l2)));
-    }
+    if (edge)
+      drow[ei] = to_bf16((ei == y) ? dy : w * exp2_hw(__builtin_fmaf(bf16_to_f32(zrow[ei]), kLog2e, -l2)));
   }
   if (threadIdx.x == 0) flush_stats(a, sc);
+}
+
+template <int NT, int NC>
+__global__ __launch_bounds__(NT) void rows_bf16_prefix(RowArgs a) {
+  bf16_prefix_rows<NT, NC, false>(a);
+}
+template <int NT, int NC>
+__global__ __launch_bounds__(NT) void rows_bf16_prefix_phase(RowArgs a) {
+  bf16_prefix_rows<NT, NC, true>(a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1550,6 +1544,12 @@ const void* pick_bf16(int i) {
     default: return (const void*)rows_bf16_resident<1024, 19, BWD>;
   }
 }
+template <typename Tin, bool BWD>
+const void* pick_stream(bool aligned, bool phase_ok) {
+  if (aligned) return (const void*)rows_stream<Tin, 1024, BWD, true>;
+  if (phase_ok) return (const void*)rows_stream<Tin, 1024, BWD, false>;
+  return (const void*)rows_stream_entries<Tin, 1024, BWD>;
+}
 template <bool BWD>
 const void* pick_f32(int i) {
   switch (i) {
@@ -1575,14 +1575,15 @@ RowLaunch select_row_kernel(int32_t dtype, int64_t V, bool aligned, bool bwd, in
   int64_t chunks = (V * esize + 15) / 16;
   int pick = -1;
   const bool whole_chunks = (V * esize) % 16 == 0;
-  // a row with a phase touches at most ceil((V + 7) / 8) chunks (ceil(V / 8) when every row
-  // starts on a 16-byte boundary)
-  const bool ph = !(aligned && whole_chunks) && dtype == DPPO_BF16 && phase_ok;
-  if (ph && !aligned) chunks = (V + 14) / 8;
-  // fp32 rows on an aligned stride may end in a partial chunk: rows_f32_resident loads and
-  // stores its last V % 4 entries one by one
-  const bool f32_ragged = dtype == DPPO_F32 && aligned && !whole_chunks;
-  if (((aligned && whole_chunks) || ph || f32_ragged) && !(force & kForceStream)) {
+  // bf16 rows that are not aligned or not whole chunks take the phase kernels; the fp32 and the
+  // prefix kernels take rows that start and end anywhere. A row that starts anywhere touches at
+  // most ceil((V + E - 1) / E) chunks of E entries, and holds at least floor((V - E + 1) / E)
+  // whole ones.
+  phase_ok = phase_ok || aligned;
+  const bool ph = dtype == DPPO_BF16 && !(aligned && whole_chunks);
+  const int E = 16 / esize;
+  if (!aligned) chunks = (V + 2 * E - 2) / E;
+  if (phase_ok && !(force & kForceStream)) {
     for (int i = 0; i < kNumResident; ++i) {
       if ((int64_t)kResident[i].nt * kResident[i].nc >= chunks) {
         pick = i;
@@ -1617,10 +1618,13 @@ RowLaunch select_row_kernel(int32_t dtype, int64_t V, bool aligned, bool bwd, in
   }
   L.threads = 1024;
   L.resident = false;
-  if (bwd && aligned && !(force & kForceStream) && (V * esize) / 16 >= (int64_t)1024 * kPrefixNC) {
-    // longer rows: a resident prefix of 1024 x kPrefixNC whole chunks, the rest (and a
-    // ragged end) streamed twice
+  const int64_t whole = (aligned ? V : V - E + 1) / E;
+  if (bwd && phase_ok && !(force & kForceStream) && whole >= (int64_t)1024 * kPrefixNC) {
+    // longer rows: a resident prefix of 1024 x kPrefixNC whole chunks, the rest (and the
+    // entries at the ends) streamed twice
+    L.phase = dtype == DPPO_BF16 && !aligned;
     L.fn = dtype == DPPO_F32 ? (const void*)rows_f32_prefix<1024, kPrefixNC>
+           : L.phase         ? (const void*)rows_bf16_prefix_phase<1024, kPrefixNC>
                              : (const void*)rows_bf16_prefix<1024, kPrefixNC>;
     L.chunks = kPrefixNC;
     L.prefix = true;
@@ -1628,17 +1632,11 @@ RowLaunch select_row_kernel(int32_t dtype, int64_t V, bool aligned, bool bwd, in
     L.fill = dtype == DPPO_F32 ? kFillF32Prefix : kFillBf16Prefix;
     return L;
   }
-  if (dtype == DPPO_BF16) {
-    L.fn = aligned ? (bwd ? (const void*)rows_stream<uint16_t, 1024, true, true>
-                          : (const void*)rows_stream<uint16_t, 1024, false, true>)
-                   : (bwd ? (const void*)rows_stream<uint16_t, 1024, true, false>
-                          : (const void*)rows_stream<uint16_t, 1024, false, false>);
-  } else {
-    L.fn = aligned ? (bwd ? (const void*)rows_stream<float, 1024, true, true>
-                          : (const void*)rows_stream<float, 1024, false, true>)
-                   : (bwd ? (const void*)rows_stream<float, 1024, true, false>
-                          : (const void*)rows_stream<float, 1024, false, false>);
-  }
+  L.aligned = aligned;
+  if (dtype == DPPO_BF16)
+    L.fn = bwd ? pick_stream<uint16_t, true>(aligned, phase_ok) : pick_stream<uint16_t, false>(aligned, phase_ok);
+  else
+    L.fn = bwd ? pick_stream<float, true>(aligned, phase_ok) : pick_stream<float, false>(aligned, phase_ok);
   return L;
 }
 

@@ -233,3 +233,84 @@ def test_random_layouts_against_the_oracle(i, dtype, T, V, extra, off, in_place,
     if dtype == "bf16":
         a, b = a.view(torch.int16), b.view(torch.int16)
     assert torch.equal(a, b), "entries outside the rows were written"
+
+
+ANY_CASES = [  # dtype, T, V, extra columns per row, element offset of row 0
+    ("f32", 40, 1, 0, 1), ("f32", 40, 2, 0, 3), ("f32", 40, 3, 3, 2), ("f32", 60, 7, 0, 0),
+    ("f32", 300, 1003, 0, 0), ("f32", 300, 1003, 2, 1), ("f32", 1200, 4101, 1, 3),
+    ("f32", 64, 50257, 0, 0), ("f32", 24, 77818, 0, 2), ("f32", 12, 77823, 0, 1),
+    ("f32", 600, 77829, 0, 1), ("f32", 20, 151937, 0, 3),
+    ("bf16", 12, 155653, 0, 1), ("bf16", 520, 155661, 0, 0), ("bf16", 12, 262143, 4, 3),
+]
+
+
+@pytest.mark.parametrize("dtype,T,V,extra,off", ANY_CASES,
+                         ids=[f"{c[0]}_T{c[1]}_V{c[2]}_x{c[3]}_o{c[4]}" for c in ANY_CASES])
+def test_rows_that_start_anywhere(dtype, T, V, extra, off):
+    """fp32 rows at any offset (shorter than a chunk, the resident shapes' limits, the prefix
+    kernel's and the gap between them, which streams) and bf16 rows longer than the resident
+    kernels: sampled ids at the first and last entries, in the whole chunks and in the entries
+    before and after them, masked rows, a bad id, -inf at the row ends, a NaN row; the loss
+    with dlogits (entries outside the rows untouched), in place, without dlogits, and the
+    log-prob call, which agree bit for bit where they run the same kernel family."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    E = 4 if dtype == "f32" else 8
+    ld = V + extra
+    _say("rows anywhere", dtype, T, V, ld, off)
+    g = torch.Generator(device=DEV).manual_seed(V + off)
+    n = off + T * ld + 16
+    buf = (torch.randn(n, generator=g, device=DEV) * 3).to(dt)
+    z = buf[off:off + T * ld].view(T, ld)[:, :V]
+    if V > 3 * E:
+        z[8, 0] = -float("inf")
+        z[8, V - 1] = -float("inf")
+    ids = torch.randint(0, V, (T,), generator=g, device=DEV)
+    ids[0], ids[1], ids[5] = V - 1, 0, V + 3
+    for i in range(min(12, V)):
+        ids[10 + 2 * i % (T - 10)] = i               # every entry of the first chunks
+        ids[11 + 2 * i % (T - 11)] = V - 1 - i
+    mask = torch.ones(T, dtype=torch.uint8, device=DEV)
+    mask[3::7] = 0
+    anchor = oracle_anchor(z, ids.clamp(0, V - 1)).to(DEV)
+    lp_ref = (anchor + 0.2 * torch.randn(T, generator=g, device=DEV, dtype=torch.float64)).float()
+    lp_ref = lp_ref.nan_to_num(-7.0, neginf=-7.0)
+    lp_mu = (lp_ref.double() + 0.1 * torch.randn(T, generator=g, device=DEV, dtype=torch.float64)).float()
+    adv = torch.randn(T, generator=g, device=DEV)
+    dbuf = torch.full_like(buf, SENTINEL)
+    d = dbuf[off:off + T * ld].view(T, ld)[:, :V]
+    params = oracle_params((0.5, 2.0), (0.2, 0.2), "mask_weight", "const", 1.0)
+    kw = dict(scale_mode="const")
+    res = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, dlogits=d, **kw)
+    fwd = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, want_dlogits=False, **kw)
+    lp = P.logprob_fwd(z, ids.clamp(0, V - 1))
+    torch.cuda.synchronize()
+    ref = run_oracle(z, ids, lp_mu, lp_ref, adv, mask, None, params)
+    compare_loss(res, ref, params, dt)
+    compare_loss(fwd, ref, params, dt, check_dlogits=False)
+    good = ((mask != 0) & (ids < V) & torch.isfinite(res.logp)).cpu().numpy()
+    got, want = lp.cpu().double().numpy()[good], ref["lp"][good]
+    assert np.all(np.abs(got - want) <= 2e-5 * np.maximum(np.abs(want), 1.0))
+    out = _outside(dbuf, off, T, ld, V)
+    assert torch.all(dbuf[out] == SENTINEL), "entries outside the rows were written"
+    zin = buf.clone()
+    zz = zin[off:off + T * ld].view(T, ld)[:, :V]
+    P.decoupled_ppo_loss_fwd_bwd(zz, ids, lp_mu, lp_ref, adv, mask, dlogits=zz, **kw)
+    torch.cuda.synchronize()
+    it = torch.int32 if dt == torch.float32 else torch.int16
+    assert torch.equal(zz.contiguous().view(it), d.contiguous().view(it)), "in place differs"
+    assert torch.equal(zin[out].view(it), buf[out].view(it))
+    # dlogits at another offset within 16 bytes: the streaming kernel, one entry at a time
+    if off == 0 and V < 60000:
+        dbuf = torch.full_like(buf, SENTINEL)
+        d2 = dbuf[1:1 + T * ld].view(T, ld)[:, :V]
+        res = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, dlogits=d2, **kw)
+        torch.cuda.synchronize()
+        compare_loss(res, ref, params, dt)
+        assert torch.all(dbuf[_outside(dbuf, 1, T, ld, V)] == SENTINEL)
+    # a NaN in an entry at an end reaches the whole row
+    z[9] = float("nan") if V == 1 else z[9]
+    z[9, V - 1] = float("nan")
+    ids[9], mask[9] = 0, 1
+    res = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, dlogits=d, **kw)
+    torch.cuda.synchronize()
+    assert torch.isnan(res.logp[9]) and torch.isnan(d[9]).all()
