@@ -107,7 +107,7 @@ hipError_t resident_slots(const dppo::RowLaunch& L, int64_t* slots) {
 
 dppo_status launch_rows(const dppo::RowLaunch& L, const dppo::RowArgsV& args, int64_t T,
                         hipStream_t st) {
-  int64_t grid = T;
+  int64_t grid = (T + L.rows_per_group - 1) / L.rows_per_group;
   if (L.persistent) {
     int64_t slots = 0;
     const hipError_t oe = resident_slots(L, &slots);
@@ -461,8 +461,14 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
   // workgroup to read the mask counts the valid tokens itself and loss_sum takes the
   // counters from the flags, so prep_stats does not run (one launch fewer per call: the
   // tiny configuration's step 40.6 -> 36.6 us).
-  const bool count_mode = T > 0 && T <= dppo::kCountModeMaxT && L.persistent && L.counts &&
-                          flags_out != nullptr && !(g_path_policy & kPolicyAtomicCounts);
+  // A call that writes flags takes the counters from them in loss_sum: the row kernels' counter
+  // atomics serialise (one add per workgroup and counter, five addresses): T = 4573, V = 1521
+  // bf16 63 us with 1512 workgroups' atomics. The single-buffer bf16 gradient kernels of long
+  // rows keep theirs (few workgroups): the test at their end made the 1024 x 19 kernel 1.5 %
+  // slower.
+  const bool flag_counts = T > 0 && flags_out != nullptr && L.flag_counts &&
+                           !(g_path_policy & kPolicyAtomicCounts);
+  const bool count_mode = flag_counts && T <= dppo::kCountModeMaxT && L.persistent && L.counts;
   hipError_t e = hipSuccess;
   if (!count_mode) {
     dppo::launch_prep_stats(loss_mask, T, stats_out, st);
@@ -498,11 +504,12 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
     a.rd_mode = p->rd_mode;
     a.scale_mode = p->scale_mode;
     a.count_mode = count_mode ? 1 : 0;
+    a.flag_counts = flag_counts ? 1 : 0;
     s = launch_rows(L, a, T, st);
     if (s != DPPO_OK) return s;
   }
   dppo::launch_loss_sum(loss_tok_out, loss_mask, token_scale, stats_out, T, p->loss_scale,
-                        p->scale_mode, loss_out, st, count_mode ? flags_out : nullptr,
+                        p->scale_mode, loss_out, st, flag_counts ? flags_out : nullptr,
                         p->rd_mode);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "loss_sum launch");

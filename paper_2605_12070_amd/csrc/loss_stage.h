@@ -49,8 +49,9 @@ struct RowArgs {
                         // in s_sleep(6) units (set by the launcher from RowLaunch)
   int32_t count_mode;   // 1 (persistent fp32 resident loss calls that write flags): no
                         // prep_stats; each workgroup counts the valid tokens itself for the
-                        // token-mean scale (workgroup 0 stores the count), no counter
-                        // atomics; loss_sum derives the counters from the flags
+                        // token-mean scale (workgroup 0 stores the count)
+  int32_t flag_counts;  // 1 (calls that write flags): no counter atomics; loss_sum derives the
+                        // counters from the flags
 };
 
 // Arguments of the kernels without the backward sweep: the row arguments plus an optional
@@ -76,6 +77,9 @@ struct RowLaunch {
   bool prefix = false;       // backward kernel with a resident prefix and a streamed tail
   bool phase = false;        // bf16 resident kernel for rows with a phase (rows_bf16_*phase*)
   bool aligned = false;      // streaming kernel: its last template argument
+  bool flag_counts = true;   // the kernel leaves the counters to the flags when told to (all but
+                             // the single-buffer bf16 gradient kernels of long rows)
+  int rows_per_group = 1;    // rows a workgroup works on at a time
   bool counts = false;       // the kernel supports count mode (RowArgs::count_mode)
   int fill = 27;             // persistent grids: workgroups launched per 32 resident slots
   int stagger = 2;           // RowArgs::stagger for the kernels that stagger their starts

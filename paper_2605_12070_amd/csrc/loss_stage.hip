@@ -2,8 +2,8 @@
 // MIS token math (Eq. 1-4 of arXiv 2605.12070) and the fused dlogits sweep, plus the two
 // small kernels around them (valid-token count, deterministic loss sum).
 //
-// Launch shape: each token row is handled by one workgroup (persistent workgroups loop over
-// rows). A row of V = 151936 bf16 logits (297 KiB) is loaded once with 16-byte loads and
+// Launch shape: a short row is handled by one wave, a longer one by one workgroup (persistent
+// workgroups loop over rows). A row of V = 151936 bf16 logits (297 KiB) is loaded once with 16-byte loads and
 // kept in registers (1024 threads x 19 x 16 B); the thread's exponentials replace the
 // logits in the same registers as fp16 pairs, so the backward sweep reads nothing from
 // memory and writes dlogits once with 16-byte non-temporal stores. bf16 rows that start
@@ -55,8 +55,8 @@ __device__ __forceinline__ bool version_ok(const A& a, int64_t row) {
 // The call's loss scale (Eq. 2: the token-mean normaliser, or the constant), once per
 // workgroup; every thread calls it. Normally prep_stats has stored the valid-token count; in
 // count mode the workgroup counts the mask itself (workgroup 0 also stores the count, for
-// loss_sum), which saves that launch for a short batch. The fp32 resident kernel (before
-// its first row) and the bf16 kernels with two row buffers (behind their first row's loads)
+// loss_sum), which saves that launch for a short batch. The short-row kernels and the fp32 resident kernel (before
+// their first row) and the bf16 kernels with two row buffers (behind their first row's loads)
 // take this path; in the single-buffer bf16 kernels the extra prologue cost 0.7 % of the
 // flagship's time even with count mode off. Counting behind the first row's loads in the
 // fp32 kernel too was measured slower (the tiny batch's step 27.5 us against 25.6 us).
@@ -184,6 +184,232 @@ __device__ __forceinline__ void finish_row(const RowArgs& a, int64_t row, float 
     bc->w = o.w;
     bc->lse2 = lse2;
     bc->dy = o.dy;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// Short rows (at most 256 NC 16-byte chunks): one wave per row, four rows per workgroup.
+//
+// Bound by latency, not by bytes: with a workgroup per row, a row of a few KB was a chain of a
+// load, a barrier, the token math on one thread, another barrier and the stores, with little in
+// flight on each CU. A wave needs no barrier and no LDS broadcast (every lane runs the token
+// math on the same values), and up to 32 rows of a CU are in flight at once. A lane holds up to
+// 4 NC chunks; chunks no lane of the wave has are skipped by uniform branches. The numerics are
+// those of resident_rows for bf16 (an integer log2 shift per chunk, exponentials kept as fp16
+// pairs); an fp32 row is shifted by its maximum, as the general kernels' merged result is, and
+// keeps fp32 exponentials.
+// Rows may start and end anywhere: a row is read as the aligned chunks that cover it, entries of
+// the neighbouring rows count as -inf and are never written (see resident_rows; dlogits has the
+// logits' phase). Whole calls, with the counter atomics gone as well (forward and backward, as
+// workgroups per row against this): bf16 T = 4573, V = 1521 70 -> 23 us, T = 5065, V = 6373
+// 80 -> 39 us, T = 16384, V = 8192 134 -> 117 us; fp32 T = 16384, V = 2000 67 -> 63 us, V = 4000
+// the same; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, T = 13324, V = 1616 fp32 33 -> 16 us.
+// ---------------------------------------------------------------------------------------
+constexpr int kWaveNT = 256;
+
+template <typename Tin, int NC, bool BWD>
+__device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
+  constexpr bool BF = sizeof(Tin) == 2;
+  constexpr int E = 16 / (int)sizeof(Tin);
+  constexpr int M = NC * kWaveNT / 64;       // chunks per lane
+  constexpr int NW = kWaveNT / 64;           // rows per workgroup
+  // shifts of a lane's chunks (bf16), [c][tid]: conflict-free, read back by the lane that wrote
+  __shared__ float nch[BWD && BF ? M : 1][kWaveNT];
+  __shared__ int counts[NW][4];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool loss_mode = a.mode != kModeLogprob;
+  const float scale = call_scale<kWaveNT>(a);
+  const int V = a.V;
+  StatCount sc;
+  for (int64_t row = (int64_t)blockIdx.x * NW + wv; row < a.T; row += (int64_t)gridDim.x * NW) {
+    // the row's scalar loads, all issued before the first branch on any of them
+    const uint32_t mword =
+        (loss_mode && a.mask != nullptr)
+            ? uload((const uint32_t*)(((uintptr_t)a.mask + (uintptr_t)row) & ~(uintptr_t)3))
+            : 0xffffffffu;
+    const int64_t y = uload(a.ids + row);
+    const TokenIn tin = token_inputs(a, row, scale);
+    const Tin* zrow = row_ptr<Tin>(a, row);
+    const bool valid = ((mword >> (8u * (uint32_t)(((uintptr_t)a.mask + (uintptr_t)row) & 3u))) & 0xffu) != 0;
+    const bool good = (y >= 0) && (y < V) && version_ok(a, row);
+    if (loss_mode && !(valid && good)) {
+      if (BWD && a.dlogits) {
+        Tin* d = (Tin*)a.dlogits + row * a.ldd;
+        const RowSplit sp = split_row(d, V);
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        for (int i = lane; i < sp.nfull; i += 64) __builtin_nontemporal_store(z, (u32x4*)(d + sp.lead) + i);
+        if (lane < sp.nedge) d[sp.template entry<E>(lane)] = (Tin)0;
+      }
+      if (lane == 0) {
+        a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
+        a.loss_tok[row] = 0.0f;
+        if (a.flags) a.flags[row] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
+        if (valid) sc.bad += 1;
+      }
+      continue;
+    }
+    // entry k of this lane's chunk c lies inside the row iff lo(c) <= k < hi(c)
+    const int ph = (int)(((uintptr_t)zrow / sizeof(Tin)) & (E - 1));
+    const int end = ph + V;                  // in entries from the first chunk's start
+    const int bytes = ((end + E - 1) / E) * 16;
+    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow - ph, bytes);
+    const int voff = lane * 16;
+    auto lo = [&](int c) { return ph - E * (c * 64 + lane); };
+    auto hi = [&](int c) { return end - E * (c * 64 + lane); };
+    auto any = [&](int c) { return E * c * 64 < end; };                    // uniform
+    auto whole = [&](int c) { return (c > 0 || ph == 0) && E * (c + 1) * 64 <= end; };
+    uint32_t r[M][4];
+#pragma unroll
+    for (int c = 0; c < M; ++c) load16<kAuxLast>(r[c], rz, voff, c * 1024);
+    // z[y] (a bad id of a log-prob call reads the row's first entry, unused)
+    const uintptr_t at = (uintptr_t)(zrow + (good ? y : 0));
+    const uint32_t zword = uload((const uint32_t*)(at & ~(uintptr_t)3));
+    const float zy = !good ? 0.0f : (!BF ? __uint_as_float(zword) : ((at & 2u) ? bf16_hi(zword) : bf16_lo(zword)));
+
+    float N = -INFINITY, S = 0.0f;
+    // chunk c as floats, entries outside the row -inf
+    auto entries = [&](int c, float (&x)[E]) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (BF) {
+          x[2 * k] = bf16_lo(r[c][k]);
+          x[2 * k + 1] = bf16_hi(r[c][k]);
+        } else {
+          x[k] = __uint_as_float(r[c][k]);
+        }
+      }
+      if (!whole(c)) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) x[k] = (k >= lo(c) && k < hi(c)) ? x[k] : -INFINITY;
+      }
+    };
+    if constexpr (BF) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        if (!any(c)) continue;
+        float x[E];
+        entries(c, x);
+        const float cm = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7]));
+        float nc = __builtin_ceilf(cm * kLog2e);
+        const float sh = (nc == -INFINITY) ? 0.0f : nc;
+        float e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = exp2_hw(__builtin_fmaf(x[j], kLog2e, -sh));
+        const float cs = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+        if (BWD) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            r[c][k] = pack_f16(e[2 * k], e[2 * k + 1]);
+            asm volatile("" : "+v"(r[c][k]));
+          }
+          nch[c][tid] = nc;
+        }
+        merge_ns_int(N, S, nc, cs);
+        asm volatile("" : "+v"(N), "+v"(S));
+      }
+    } else {
+      float m = -INFINITY;
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        if (!any(c)) continue;
+        float x[E];
+        entries(c, x);
+        m = max3(m, x[0], x[1]);
+        m = max3(m, x[2], x[3]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[c][k] = __float_as_uint(x[k]);
+      }
+      m = wave_max(m);
+      N = (m == -INFINITY) ? -INFINITY : m * kLog2e;
+      const float sh = (m == -INFINITY) ? 0.0f : N;
+      float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        if (!any(c)) continue;
+        float e[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          e[j] = exp2_hw(__builtin_fmaf(__uint_as_float(r[c][j]), kLog2e, -sh));
+          if (BWD) r[c][j] = __float_as_uint(e[j]);
+        }
+        s0 += e[0]; s1 += e[1]; s2 += e[2]; s3 += e[3];
+      }
+      S = wave_sum((s0 + s1) + (s2 + s3));
+    }
+    if constexpr (BF) wave_merge_ns_int(N, S);   // every lane has the row's sum
+    const float lse2 = (N == -INFINITY) ? __builtin_nanf("") : N + log2f(S);
+    if (!loss_mode) {
+      if (lane == 0) {
+        a.lp_out[row] = good ? zy - lse2 * kLn2 : __builtin_nanf("");
+        if (a.lse_out) a.lse_out[row] = lse2 * kLn2;
+      }
+      continue;
+    }
+    const TokenOut o = token_math(a, tin, zy, lse2);
+    if (lane == 0) {
+      a.lp_out[row] = o.lp;
+      a.loss_tok[row] = o.loss;
+      if (a.flags) a.flags[row] = o.flags;
+      count_stats(a, o.flags, sc);
+    }
+    if (!BWD || !a.dlogits) continue;
+    Tin* drow = (Tin*)a.dlogits + row * a.ldd;
+    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow - ph, bytes);
+    const float ff = row_factor(o.w, N, lse2);      // fp32
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      if (!any(c)) continue;
+      u32x4 v;
+      if constexpr (BF) {
+        const float ncv = nch[c][tid];
+        const float f = (lse2 != lse2) ? lse2 : ((ncv == -INFINITY) ? 0.0f : o.w * exp2_hw(ncv - lse2));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = pack_bf16(f16_lo_mul(r[c][k], f), f16_hi_mul(r[c][k], f));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__uint_as_float(r[c][k]) * ff);
+      }
+      if (whole(c) || (lo(c) <= 0 && hi(c) >= E)) {
+        buf_store16_nt(v, rd, voff, c * 1024);
+      } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          if (k >= lo(c) && k < hi(c)) {
+            if constexpr (BF)
+              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[k >> 1] >> (16 * (k & 1))), rd, voff + 2 * k,
+                                                    c * 1024, kAuxNT);
+            else
+              __builtin_amdgcn_raw_buffer_store_b32(v[k], rd, voff + 4 * k, c * 1024, kAuxNT);
+          }
+        }
+      }
+    }
+    // the sampled entry, by the lane whose chunk holds it, behind that chunk's store (two
+    // stores of one lane to one address, through the same path, land in program order)
+    const int ey = (int)y + ph;
+    if (lane == ((ey / E) & 63)) {
+      if constexpr (BF) __builtin_amdgcn_raw_buffer_store_b16(to_bf16(o.dy), rd, ey * 2, 0, kAuxNT);
+      else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.dy), rd, ey * 4, 0, kAuxNT);
+    }
+  }
+  if (a.flag_counts || !loss_mode) return;   // uniform over the grid
+  if (lane == 0) {
+    counts[wv][0] = sc.band;
+    counts[wv][1] = sc.ppo;
+    counts[wv][2] = sc.active;
+    counts[wv][3] = sc.bad;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int i = 1; i < NW; ++i) {
+      sc.band += counts[i][0];
+      sc.ppo += counts[i][1];
+      sc.active += counts[i][2];
+      sc.bad += counts[i][3];
+    }
+    flush_stats(a, sc);
   }
 }
 
@@ -520,18 +746,19 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
   } else {
     for (; row < a.T; row += gridDim.x) step(r1, r1, false);
   }
-  // count mode: loss_sum derives the counters from the flags
-  if (threadIdx.x == 0 && !(DB && a.count_mode)) flush_stats(a, sc);
+  if (threadIdx.x == 0 && !(DB && a.count_mode)) add_stats(a, sc);
 }
 
 template <int NT, int NC, bool BWD>
 __global__ __launch_bounds__(NT) void rows_bf16_resident(RowArgsOf<BWD> a) {
-  resident_rows<NT, NC, BWD, false, false>(a);
+  if constexpr (NT == kWaveNT) wave_rows<uint16_t, NC, BWD>(a);
+  else resident_rows<NT, NC, BWD, false, false>(a);
 }
 // Rows with a phase (see resident_rows).
 template <int NT, int NC, bool BWD>
 __global__ __launch_bounds__(NT) void rows_bf16_phase(RowArgsOf<BWD> a) {
-  resident_rows<NT, NC, BWD, false, true>(a);
+  if constexpr (NT == kWaveNT) wave_rows<uint16_t, NC, BWD>(a);
+  else resident_rows<NT, NC, BWD, false, true>(a);
 }
 // The two-buffer form, with dlogits (the backward kernel).
 template <int NT, int NC>
@@ -660,11 +887,13 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
 
 template <int NT, int NC>
 __global__ __launch_bounds__(NT) void rows_bf16_fwd(RowArgsV a) {
-  fwd_rows<NT, NC, false>(a);
+  if constexpr (NT == kWaveNT) wave_rows<uint16_t, NC, false>(a);
+  else fwd_rows<NT, NC, false>(a);
 }
 template <int NT, int NC>
 __global__ __launch_bounds__(NT) void rows_bf16_fwd_phase(RowArgsV a) {
-  fwd_rows<NT, NC, true>(a);
+  if constexpr (NT == kWaveNT) wave_rows<uint16_t, NC, false>(a);
+  else fwd_rows<NT, NC, true>(a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -675,7 +904,7 @@ __global__ __launch_bounds__(NT) void rows_bf16_fwd_phase(RowArgsV a) {
 // twice, 4 bytes per lane) and takes 0.33 ms here.
 // ---------------------------------------------------------------------------------------
 template <int NT, int NC, bool BWD>
-__global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
+__device__ __forceinline__ void f32_resident_rows(const RowArgsOf<BWD>& a) {
   __shared__ float red[2 * (NT / 64) + 2];
   __shared__ Bcast bc;
   StatCount sc;
@@ -785,8 +1014,13 @@ __global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
     if (edge) drow[ei] = (ei == y) ? dy : ee * f;
   };
   for (int64_t row = blockIdx.x; row < a.T; row += gridDim.x) one(row);
-  // in count mode the counters come from the flags (loss_sum)
-  if (threadIdx.x == 0 && !a.count_mode) flush_stats(a, sc);
+  if (threadIdx.x == 0) flush_stats(a, sc);
+}
+
+template <int NT, int NC, bool BWD>
+__global__ __launch_bounds__(NT) void rows_f32_resident(RowArgsOf<BWD> a) {
+  if constexpr (NT == kWaveNT) wave_rows<float, NC, BWD>(a);
+  else f32_resident_rows<NT, NC, BWD>(a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1426,8 +1660,7 @@ constexpr ResCfg kResident[] = {{256, 1},  {256, 2},   {256, 4},   {512, 4},   {
 constexpr int kNumResident = sizeof(kResident) / sizeof(kResident[0]);
 // Per-shape launch choices, each from same-box A/B timings at T = 16384 (MI355X):
 //  * bf16 backward with two row buffers: 5-10 % faster for 512 x 4 .. 1024 x 8; within
-//    +-4 % (either way) for the 256-thread shapes and 1024 x 12; 1024 x 19 has no registers
-//    for a second row;
+//    +-4 % (either way) for 1024 x 12; 1024 x 19 has no registers for a second row;
 //  * fp32 persistent (a loop over rows, counters flushed once per workgroup) rather than one
 //    workgroup per row: 2-6x faster up to 512 x 8 and 6 % at 1024 x 19, 0-7 % slower for
 //    1024 x 6 .. 1024 x 12.
@@ -1447,13 +1680,13 @@ constexpr bool kF32Persistent[kNumResident] = {true,  true,  true,  true,  true,
 // 0.6 % shorter, 32: 0.3 % shorter; same-process runs), the same time at
 // T = 16384, 0.3-0.5 % less at T = 8192 and 1-2 % more at T = 2048.
 // Shapes:                                   256x1 256x2 256x4 512x4 512x6 512x8 1Kx6 1Kx8 1Kx12 1Kx19
-constexpr int kFillBf16Bwd[kNumResident] = {27,   27,   27,   32,   29,   31,   27,  27,  29,   27};
-constexpr int kFillBf16Fwd[kNumResident] = {30,   30,   30,   32,   32,   32,   32,  32,  30,   30};
-constexpr int kFillF32Bwd[kNumResident] = {27,    27,   27,   30,   30,   30,   27,  27,  27,   25};
-constexpr int kFillF32Fwd[kNumResident] = {27,    27,   27,   32,   32,   32,   27,  27,  27,   32};
-// Measured: bf16 backward from 256 x 4 up; bf16 forward all but 256 x 2; fp32 backward
-// 512 x 4, 512 x 8 and 1024 x 19; fp32 forward 512 x 4 and 1024 x 19. fp32 backward
-// 1024 x 6 .. 12 run one workgroup per row (kF32Persistent), so their fill is unused.
+constexpr int kFillBf16Bwd[kNumResident] = {32,   32,   32,   32,   29,   31,   27,  27,  29,   27};
+constexpr int kFillBf16Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   32,  32,  30,   30};
+constexpr int kFillF32Bwd[kNumResident] = {32,   32,   32,   30,   30,   30,   27,  27,  27,   25};
+constexpr int kFillF32Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   27,  27,  27,   32};
+// Measured: bf16 backward and forward; the 256-thread kernels (a row per wave) 32 against 27
+// (2-5 % slower) and 24 (2 % either way); fp32 backward 512 x 4, 512 x 8 and 1024 x 19; fp32
+// forward 512 x 4 and 1024 x 19. fp32 backward 1024 x 6 .. 12 run one workgroup per row (kF32Persistent), so their fill is unused.
 constexpr int kFillF32Prefix = 32;
 constexpr int kFillBf16Prefix = 31;
 // Start stagger of the persistent bf16 kernels (RowArgs::stagger: s_sleep(6) units per
@@ -1604,9 +1837,11 @@ RowLaunch select_row_kernel(int32_t dtype, int64_t V, bool aligned, bool bwd, in
                         : pick_bf16_fwd(pick))
                  : (bwd ? pick_f32<true>(pick) : pick_f32<false>(pick));
     L.two_buffers = dtype == DPPO_BF16 && bwd && kResidentDB[pick];
-    // the fp32 resident kernel and the bf16 two-buffer kernels can count the valid tokens
-    // themselves (count mode)
-    L.counts = dtype == DPPO_F32 || L.two_buffers;
+    // the short-row kernels, the fp32 resident kernel and the bf16 two-buffer kernels can
+    // count the valid tokens themselves (count mode)
+    L.counts = dtype == DPPO_F32 || L.two_buffers || L.threads == kWaveNT;
+    L.flag_counts = L.counts || !bwd;
+    if (L.threads == kWaveNT) L.rows_per_group = kWaveNT / 64;
     L.resident = true;
     // fp32 forward rows loop persistently at every shape: 0-2.5 % faster than one workgroup
     // per row for 1024 x 6 .. 12 (the gradient kernel there is 0-6 % slower persistent)

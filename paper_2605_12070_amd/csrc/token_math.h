@@ -103,7 +103,8 @@ __device__ __forceinline__ float row_scale(const RowArgs& a) {
 
 // A workgroup's counters, kept by thread 0 over all of its rows and added to the global
 // counters once, when the workgroup ends: device-scope atomics on the same five addresses
-// serialise, and one per row made a batch of short rows wait on them.
+// serialise, and one per row made a batch of short rows wait on them. In a call that writes
+// flags nothing is added here: loss_sum derives the counters from them.
 struct StatCount {
   int band = 0, ppo = 0, active = 0, bad = 0;
 };
@@ -117,11 +118,14 @@ __device__ __forceinline__ void count_stats(const RowArgs& a, uint8_t flags, Sta
   sc.active += ppo && (band || !uses_mask);
 }
 
-__device__ __forceinline__ void flush_stats(const RowArgs& a, const StatCount& sc) {
+__device__ __forceinline__ void add_stats(const RowArgs& a, const StatCount& sc) {
   if (sc.band) atomicAdd(&a.stats[DPPO_STAT_N_BAND], sc.band);
   if (sc.ppo) atomicAdd(&a.stats[DPPO_STAT_N_PPO], sc.ppo);
   if (sc.active) atomicAdd(&a.stats[DPPO_STAT_N_ACTIVE], sc.active);
   if (sc.bad) atomicAdd(&a.stats[DPPO_STAT_N_BAD], sc.bad);
+}
+__device__ __forceinline__ void flush_stats(const RowArgs& a, const StatCount& sc) {
+  if (!a.flag_counts) add_stats(a, sc);
 }
 
 

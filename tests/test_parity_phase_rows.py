@@ -314,3 +314,61 @@ def test_rows_that_start_anywhere(dtype, T, V, extra, off):
     res = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, dlogits=d, **kw)
     torch.cuda.synchronize()
     assert torch.isnan(res.logp[9]) and torch.isnan(d[9]).all()
+
+
+SHORT_CASES = [  # dtype, T, V, extra columns per row, element offset of row 0
+    ("bf16", 41, 2, 0, 5), ("bf16", 42, 8, 0, 0), ("bf16", 43, 511, 0, 1), ("bf16", 41, 512, 8, 0),
+    ("bf16", 90, 513, 1, 7), ("bf16", 37, 2041, 0, 7), ("bf16", 64, 2048, 0, 0), ("bf16", 33, 2049, 0, 0),
+    ("bf16", 30, 4089, 7, 7), ("bf16", 31, 4096, 0, 0), ("bf16", 30, 4097, 0, 3), ("bf16", 29, 8185, 0, 7),
+    ("bf16", 5000, 600, 0, 3),
+    ("f32", 43, 255, 0, 1), ("f32", 41, 256, 0, 0), ("f32", 42, 1021, 0, 3), ("f32", 41, 1024, 4, 0),
+    ("f32", 33, 1025, 0, 0), ("f32", 30, 2045, 0, 3), ("f32", 31, 2048, 0, 0), ("f32", 29, 4093, 0, 3),
+    ("f32", 30, 4096, 0, 0), ("f32", 5000, 300, 0, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,T,V,extra,off", SHORT_CASES,
+                         ids=[f"{c[0]}_T{c[1]}_V{c[2]}_x{c[3]}_o{c[4]}" for c in SHORT_CASES])
+def test_short_rows_one_wave_each(dtype, T, V, extra, off):
+    """Rows that one wave works on: the ends of each capacity, of a wave's 64 chunks, and
+    batches that leave waves of the last workgroup without a row."""
+    name = P.row_kernel_name(torch.float32 if dtype == "f32" else torch.bfloat16, V, V + extra)
+    assert "<256, " in name, name
+    test_rows_that_start_anywhere(dtype, T, V, extra, off)
+
+
+@pytest.mark.parametrize("dtype,T,V,grads", [("bf16", 1027, 700, True), ("bf16", 1027, 9001, False),
+                                             ("bf16", 515, 160001, True), ("f32", 1027, 700, True),
+                                             ("f32", 515, 30001, True), ("f32", 515, 90001, False)])
+def test_counters_from_flags_and_from_atomics(dtype, T, V, grads):
+    """The counters and the loss are the same whether loss_sum derives them from the flags or the
+    kernels add them (no flags written, or the atomics policy)."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(V)
+    z = (torch.randn(T, V, generator=g, device=DEV) * 3).to(dt)
+    ids = torch.randint(0, V, (T,), generator=g, device=DEV)
+    ids[7] = -1
+    mask = (torch.rand(T, generator=g, device=DEV) > 0.3).to(torch.uint8)
+    mask[7] = 1
+    lp = P.logprob_fwd(z, ids.clamp(0, V - 1))
+    lp_ref = lp + 0.3 * torch.randn(T, generator=g, device=DEV)
+    lp_mu = lp_ref + 0.6 * torch.randn(T, generator=g, device=DEV)
+    adv = torch.randn(T, generator=g, device=DEV)
+    for rd_mode in ("mask_weight", "weight"):
+        def call(**kw):
+            return P.decoupled_ppo_loss_fwd_bwd(z, ids, lp_mu, lp_ref, adv, mask, rd_mode=rd_mode,
+                                                want_dlogits=grads, **kw)
+        a, b = call(), call(want_flags=False)
+        P.set_path_policy("auto+atomics")
+        try:
+            c = call()
+        finally:
+            P.set_path_policy("auto")
+        torch.cuda.synchronize()
+        f = a.flags.to(torch.int32)
+        band, ppo = (f & P.FLAG_BAND) != 0, (f & P.FLAG_PPO) != 0
+        act = ppo & band if rd_mode == "mask_weight" else ppo
+        want = [int(mask.sum()), int(band.sum()), int(ppo.sum()), int(act.sum()), 1]
+        for r in (a, b, c):
+            assert r.stats.tolist() == want
+            assert torch.equal(r.loss.view(torch.int32), a.loss.view(torch.int32))
