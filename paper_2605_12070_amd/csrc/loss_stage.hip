@@ -6,10 +6,9 @@
 // workgroups loop over rows). A row of V = 151936 bf16 logits (297 KiB) is loaded once with 16-byte loads and
 // kept in registers (1024 threads x 19 x 16 B); the thread's exponentials replace the
 // logits in the same registers as fp16 pairs, so the backward sweep reads nothing from
-// memory and writes dlogits once with 16-byte non-temporal stores. bf16 rows that start
-// anywhere or end in a partial chunk run in the same kernels with the neighbouring entries
-// masked (the phase kernels); the fp32 kernels take rows that start and end anywhere as their
-// whole chunks plus a few single entries. Rows longer than the register budget keep a
+// memory and writes dlogits once with 16-byte non-temporal stores. Rows that
+// start or end anywhere are their whole aligned chunks plus a few single entries (for bf16 in
+// variants of their own, the phase kernels). Rows longer than the register budget keep a
 // resident prefix and read only the rest twice (the prefix kernels); what is left (forward
 // calls on rows past the budget, dlogits at another offset within 16 bytes than the logits)
 // uses a streaming kernel that reads the row once per pass.
@@ -25,18 +24,21 @@ namespace dppo {
 // and version_ok rejects the token. The pointer is picked with a chain of uniform selects:
 // indexing the by-value argument array with a run-time index would make the compiler copy
 // the arguments to scratch.
-template <class A>
-__device__ __forceinline__ const void* logits_of(const A& a, int64_t row) {
+__device__ __forceinline__ const void* version_logits(const RowArgsV& a, int v) {
   const void* base = a.logits;
-  if constexpr (std::is_same<A, RowArgsV>::value) {
-    if (a.version) {
-      const int v = (int)uload((const uint32_t*)(a.version + row));
+  if (a.version) {
 #pragma unroll
-      for (int i = 1; i < DPPO_MAX_VERSIONS; ++i)
-        if (v == i && i < a.nver) base = a.vlogits[i];
-    }
+    for (int i = 1; i < DPPO_MAX_VERSIONS; ++i)
+      if (v == i && i < a.nver) base = a.vlogits[i];
   }
   return base;
+}
+template <class A>
+__device__ __forceinline__ const void* logits_of(const A& a, int64_t row) {
+  if constexpr (std::is_same<A, RowArgsV>::value)
+    return version_logits(a, a.version ? (int)uload((const uint32_t*)(a.version + row)) : 0);
+  else
+    return a.logits;
 }
 template <class T, class A>
 __device__ __forceinline__ const T* row_ptr(const A& a, int64_t row) {
@@ -140,6 +142,21 @@ __device__ void zero_row(Tin* d, int V) {
   if ((int)threadIdx.x < sp.nedge) d[sp.entry<E>(threadIdx.x)] = (Tin)0;
 }
 
+// This thread's entry at an end of a bf16 row (RowSplit), 0 where it has none or rd is false.
+__device__ __forceinline__ uint16_t edge_entry(const uint16_t* row, int V, bool rd) {
+  const RowSplit sp = split_row(row, V);
+  const int i = (int)threadIdx.x;
+  return __builtin_amdgcn_raw_buffer_load_b16(row_rsrc(row, rd ? V * 2 : 0),
+                                              i < sp.nedge ? sp.entry<8>(i) * 2 : 0x7fffff00, 0, kAuxLast);
+}
+// Merges that entry into the thread's integer-shift partial.
+__device__ __forceinline__ void merge_edge(float& N, float& S, bool edge, uint16_t xe) {
+  const float x = edge ? bf16_to_f32(xe) : -INFINITY;
+  const float nc = __builtin_ceilf(x * kLog2e);
+  const float sh = (nc == -INFINITY) ? 0.0f : nc;
+  merge_ns_int(N, S, nc, exp2_hw(__builtin_fmaf(x, kLog2e, -sh)));
+}
+
 // Rows that are not evaluated (loss mask 0, or a bad token id on a valid row).
 template <typename Tin, int NT>
 __device__ void skip_row(const RowArgs& a, int64_t row, bool valid, StatCount& sc) {
@@ -199,8 +216,7 @@ __device__ __forceinline__ void finish_row(const RowArgs& a, int64_t row, float 
 // pairs); an fp32 row is shifted by its maximum, as the general kernels' merged result is, and
 // keeps fp32 exponentials.
 // Rows may start and end anywhere: a row is read as the aligned chunks that cover it, entries of
-// the neighbouring rows count as -inf and are never written (see resident_rows; dlogits has the
-// logits' phase). Whole calls, with the counter atomics gone as well (forward and backward, as
+// the neighbouring rows count as -inf and are never written (dlogits has the logits' phase). Whole calls, with the counter atomics gone as well (forward and backward, as
 // workgroups per row against this): bf16 T = 4573, V = 1521 70 -> 23 us, T = 5065, V = 6373
 // 80 -> 39 us, T = 16384, V = 8192 134 -> 117 us; fp32 T = 16384, V = 2000 67 -> 63 us, V = 4000
 // the same; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, T = 13324, V = 1616 fp32 33 -> 16 us.
@@ -436,13 +452,13 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
 // faster for the shapes 512 x 4 .. 1024 x 8 on MI355X).
 // ---------------------------------------------------------------------------------------
 // With PH (rows that do not start on a 16-byte boundary, or whose length is not a whole number
-// of chunks) a row is read as the aligned chunks that cover it, from the 16-byte boundary at
-// or below its start: the first ph = (start / 2) % 8 entries of the first chunk belong to the
-// row before, and the last chunk may run past the row's end (at most 7 entries, inside the
-// 16-byte boundary after it). Those entries are read but count as -inf in the sums, and are
-// never written: the first and last chunks of the gradient are stored entry by entry, so the
-// neighbouring rows (other workgroups' dlogits, or their logits in place) are left alone.
-// dlogits must then have the logits' phase on every row (the launcher checks it).
+// of chunks) the row's whole aligned chunks go through the registers, and each of the entries
+// before and after them (RowSplit: fewer than 8 at each end) through one register of a thread of
+// its own; dlogits must then have the logits' phase on every row (the launcher checks it). Reading
+// the aligned chunks that cover the row and masking the neighbouring rows' entries instead kept
+// masks and both stores of every chunk alive (181 registers spilled at 1024 x 19). Before and
+// now, T = 8000: forward and backward V = 120001 855 -> 761 us, V = 50257 338 -> 325 us;
+// log-probs V = 90001 284 -> 256 us, V = 32001 102 -> 93 us.
 template <int NT, int NC, bool BWD, bool DB, bool PH>
 __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
   __shared__ float red[2][2 * (NT / 64)];   // alternated merge by merge: one barrier per merge
@@ -486,19 +502,24 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
   // Every load and store of the row goes through a buffer resource; a resource with
   // num_records = 0 turns an access into a no-op (loads read zeros, stores are dropped),
   // which keeps the chunk loops free of branches.
-  // The resource over row rr's chunks (size 0 when rd is false); with PH it starts at the
-  // 16-byte boundary at or below the row and covers the chunks the row touches.
+  // The resource over row rr's chunks (size 0 when rd is false); with PH over its whole ones.
   auto load_rsrc = [&](int64_t rr, bool rd) -> __amdgpu_buffer_rsrc_t {
     const uint16_t* p = row_ptr<uint16_t>(a, rd ? rr : 0);
     if constexpr (PH) {
-      const int ph = (int)(((uintptr_t)p >> 1) & 7);
-      return row_rsrc(p - ph, rd ? ((ph + a.V + 7) >> 3) * 16 : 0);
+      const RowSplit sp = split_row(p, a.V);
+      return row_rsrc(p + sp.lead, rd ? sp.nfull * 16 : 0);
     } else {
       return row_rsrc(p, rd ? a.V * 2 : 0);
     }
   };
+  // PH: this thread's entry at an end of the row, if it has one
+  auto load_edge = [&](int64_t rr, bool rd) -> uint16_t {
+    if constexpr (PH) return edge_entry(row_ptr<uint16_t>(a, rd ? rr : 0), a.V, rd);
+    else return 0;
+  };
   uint32_t r1[NC][4];
   uint32_t r2[DB ? NC : 1][4];             // the second row buffer (DB)
+  uint16_t x1 = 0, x2 = 0;                 // PH: the rows' end entries
   StatCount sc;                            // thread 0's counters over this workgroup's rows
   int64_t row = blockIdx.x;
   // the call's scale (token-mean: from the valid-token count, fixed while the kernel runs);
@@ -518,6 +539,7 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
     const __amdgpu_buffer_rsrc_t rz = load_rsrc(row, rd_cur);
 #pragma unroll
     for (int c = 0; c < NC; ++c) load16<kAuxLast>(r1[c], rz, threadIdx.x * 16, c * NT * 16);
+    x1 = load_edge(row, rd_cur);
   }
   // In count mode the workgroup counts the mask here, its loads in flight together with the
   // first row's: one memory round trip for both, where a counting kernel before this one
@@ -532,9 +554,9 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
     asm volatile("" :: "s"(y_cur));
   }
   int parity = 0;
-  // One row: its chunks are in r (cur); nx receives the next row's chunks (nx is r itself
-  // without DB). `first`: nothing but this row's loads is outstanding.
-  auto step = [&](uint32_t (&r)[NC][4], uint32_t (&nx)[NC][4], bool first) {
+  // One row: its chunks are in r (cur) and its end entry in xe; nx and nxe receive the next
+  // row's (nx is r itself without DB). `first`: nothing but this row's loads is outstanding.
+  auto step = [&](uint32_t (&r)[NC][4], uint32_t (&nx)[NC][4], uint16_t& xe, uint16_t& nxe, bool first) {
     // Start a row only once all of it has arrived, rather than consuming chunks as they
     // land: measured faster on MI355X, by 1-2 %, with the staggered starts and the reduced
     // grid described above. Without DB this also waits for the previous row's stores; with
@@ -547,17 +569,15 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
     const int tid = threadIdx.x;
     const int V = a.V;
     const int voff = tid * 16;
-    const int nfull = V >> 3;               // 16-byte chunks of a row (V % 8 == 0 here)
+    const RowSplit sp = PH ? split_row(row_ptr<uint16_t>(a, row), V) : RowSplit{0, V >> 3, 0};
+    const int nfull = sp.nfull;             // whole 16-byte chunks of the row (all of it without PH)
     // Slots c < cb are inside the row for every thread, slot cb only for threads with
     // lane_in, slots above cb for none. Chunks outside the row read as zeros (buffer
     // range check) and are dropped from the sums and from the stores.
     const int cb = nfull / NT;
     const bool lane_in = tid < nfull - cb * NT;
-    // PH: the row's phase; entry k of this thread's chunk in slot c lies inside the row iff
-    // ph_lo(c) <= k < ph_hi(c).
-    const int ph = PH ? (int)(((uintptr_t)row_ptr<uint16_t>(a, row) >> 1) & 7) : 0;
-    auto ph_lo = [&](int c) { return ph - 8 * (c * NT + tid); };
-    auto ph_hi = [&](int c) { return ph + V - 8 * (c * NT + tid); };
+    const bool edge = PH && tid < sp.nedge;
+    const int ei = sp.entry<8>(tid);
 
     const int64_t next = row + gridDim.x;
     // Without DB, the scalar loads are all issued here and waited for only where they are
@@ -575,6 +595,7 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
       const __amdgpu_buffer_rsrc_t rn = load_rsrc(rd_next ? next : row, rd_next);
 #pragma unroll
       for (int c = 0; c < NC; ++c) load16<kAuxLast>(nx[c], rn, voff, c * NT * 16);
+      nxe = load_edge(rd_next ? next : row, rd_next);
       y = uload(a.ids + row);
     }
     const TokenIn tin = token_inputs(a, row, scale);
@@ -597,11 +618,6 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
           x[2 * k] = bf16_lo(r[c][k]);
           x[2 * k + 1] = bf16_hi(r[c][k]);
         }
-        if constexpr (PH) {                 // entries of the neighbouring rows
-          const int lo = ph_lo(c), hi = ph_hi(c);
-#pragma unroll
-          for (int k = 0; k < 8; ++k) x[k] = (k >= lo && k < hi) ? x[k] : -INFINITY;
-        }
         const float cm = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7]));
         float nc = __builtin_ceilf(cm * kLog2e);
         const float sh = (nc == -INFINITY) ? 0.0f : nc;
@@ -610,7 +626,7 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
         for (int j = 0; j < 8; ++j) e[j] = exp2_hw(__builtin_fmaf(x[j], kLog2e, -sh));
         float sc = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
         // a chunk outside the row contributes nothing
-        const bool dead = PH ? ph_hi(c) <= 0 : ((c > cb) || (c == cb && !lane_in));
+        const bool dead = (c > cb) || (c == cb && !lane_in);
         nc = dead ? -INFINITY : nc;
         sc = dead ? 0.0f : sc;
         if (BWD) {
@@ -628,6 +644,7 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
         // scheduler would otherwise unpack every chunk at once.
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (PH) merge_edge(N, S, edge, xe);
       float n = N;
       float s = S;
       block_merge_ns_int<NT>(n, s, red[parity]);
@@ -662,29 +679,10 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
     // next row's chunks. For a row that was not read the dlogits stores are dropped and
     // zeros are written below.
     uint16_t* drow = want_d ? (uint16_t*)a.dlogits + row * a.ldd : nullptr;
-    // PH: a resource from the 16-byte boundary at or below the row, over the chunks it
-    // touches (dlogits has the logits' phase)
-    uint16_t* dbase = PH ? drow - ph : drow;
-    const int dbytes = PH ? ((ph + V + 7) >> 3) * 16 : V * 2;
+    uint16_t* dbase = PH ? drow + sp.lead : drow;
+    const int dbytes = PH ? nfull * 16 : V * 2;
     const __amdgpu_buffer_rsrc_t rd = row_rsrc(dbase, (want_d && rd_cur) ? dbytes : 0);
     const float wf = rd_cur ? w : 0.0f;
-    // PH: chunk c is stored whole when it lies inside the row, else entry by entry
-    auto store_chunk = [&](const u32x4& v, const __amdgpu_buffer_rsrc_t& res, int c) {
-      if constexpr (PH) {
-        const int lo = ph_lo(c), hi = ph_hi(c);
-        if (lo <= 0 && hi >= 8) {
-          buf_store16_nt(v, res, voff, c * NT * 16);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (k >= lo && k < hi)
-              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[k >> 1] >> (16 * (k & 1))), res,
-                                                    voff + 2 * k, c * NT * 16, kAuxNT);
-        }
-      } else {
-        buf_store16_nt(v, res, voff, c * NT * 16);
-      }
-    };
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       if (BWD) {
@@ -704,10 +702,13 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
         v.y = pack_bf16(o[2], o[3]);
         v.z = pack_bf16(o[4], o[5]);
         v.w = pack_bf16(o[6], o[7]);
-        store_chunk(v, rd, c);
+        buf_store16_nt(v, rd, voff, c * NT * 16);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (PH && want_d && edge)
+      drow[ei] = !rd_cur ? (uint16_t)0
+                         : to_bf16(ei == y ? dy : w * exp2_hw(__builtin_fmaf(bf16_to_f32(xe), kLog2e, -l2)));
     // All of this row's stores are issued before any load of the next row: the vector
     // memory counter retires in order, and loads queued behind interleaved stores would
     // make every wait in the next row's pass A also wait for store acknowledgements.
@@ -716,35 +717,37 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
       const __amdgpu_buffer_rsrc_t rn = load_rsrc(rd_next ? next : row, rd_next);
 #pragma unroll
       for (int c = 0; c < NC; ++c) load16<kAuxLast>(nx[c], rn, voff, c * NT * 16);
+      nxe = load_edge(rd_next ? next : row, rd_next);
       y_cur = mt.y;
     }
     if (want_d && !rd_cur) {                // zeros for a row that was not read
       const __amdgpu_buffer_rsrc_t rz = row_rsrc(dbase, dbytes);
       const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int c = 0; c < NC; ++c) store_chunk(zero, rz, c);
+      for (int c = 0; c < NC; ++c) buf_store16_nt(zero, rz, voff, c * NT * 16);
     }
     // dlogits at v = y is w (p_y - 1) = w expm1(lp), computed once by thread 0. The thread
     // whose chunk holds y writes it over its own vector store above: two stores of one
     // thread to one address, through the same buffer path, land in program order.
-    if (want_d && rd_cur && good && tid == (int)(((y + ph) >> 3) % NT))
-      __builtin_amdgcn_raw_buffer_store_b16(to_bf16(dy), rd, (int)((y + ph) * 2), 0, kAuxNT);
+    const int yb = (int)y - sp.lead;         // within the whole chunks
+    if (want_d && rd_cur && good && (!PH || (yb >= 0 && yb < 8 * nfull)) && tid == (yb >> 3) % NT)
+      __builtin_amdgcn_raw_buffer_store_b16(to_bf16(dy), rd, yb * 2, 0, kAuxNT);
     rd_cur = rd_next;
   };
   if constexpr (DB) {
     // unrolled twice, so that the buffers swap roles without register copies
     bool first = true;
     while (row < a.T) {
-      step(r1, r2, first);
+      step(r1, r2, x1, x2, first);
       first = false;
       row += gridDim.x;
       if (row >= a.T) break;
-      step(r2, r1, false);
+      step(r2, r1, x2, x1, false);
       row += gridDim.x;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last row
   } else {
-    for (; row < a.T; row += gridDim.x) step(r1, r1, false);
+    for (; row < a.T; row += gridDim.x) step(r1, r1, x1, x1, false);
   }
   if (threadIdx.x == 0 && !(DB && a.count_mode)) add_stats(a, sc);
 }
@@ -785,22 +788,47 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
   __shared__ float red[2][2 * (NT / 64)];
   __shared__ Bcast bc;
   const bool loss_mode = a.mode != kModeLogprob;
-  auto load_rsrc = [&](int64_t rr, bool rd) -> __amdgpu_buffer_rsrc_t {
-    const uint16_t* p = row_ptr<uint16_t>(a, rd ? rr : 0);
+  // What decides whether a row is read, and from where: loaded a whole row ahead, so that no
+  // row begins with a scalar round trip (rr clamped into the batch).
+  struct RowMeta {
+    uint32_t mword;   // the 32-bit word holding the mask byte (all ones without a mask)
+    int32_t ver;
+    int64_t y;
+  };
+  auto meta_load = [&](int64_t rr) -> RowMeta {
+    const int64_t q = rr < a.T ? rr : a.T - 1;
+    RowMeta m;
+    m.mword = (loss_mode && a.mask != nullptr)
+                  ? uload((const uint32_t*)(((uintptr_t)a.mask + (uintptr_t)q) & ~(uintptr_t)3))
+                  : 0xffffffffu;
+    m.ver = a.version ? (int32_t)uload((const uint32_t*)(a.version + q)) : 0;
+    m.y = uload(a.ids + q);
+    return m;
+  };
+  auto meta_valid = [&](int64_t rr, const RowMeta& m) -> bool {
+    return ((m.mword >> (8u * (uint32_t)(((uintptr_t)a.mask + (uintptr_t)rr) & 3u))) & 0xffu) != 0;
+  };
+  auto meta_reads = [&](int64_t rr, const RowMeta& m) -> bool {
+    return !loss_mode || (meta_valid(rr, m) && m.y >= 0 && m.y < a.V);
+  };
+  auto row_at = [&](int64_t rr, int32_t ver) -> const uint16_t* {
+    return (const uint16_t*)version_logits(a, ver) + rr * a.ld;
+  };
+  auto load_rsrc = [&](int64_t rr, int32_t ver, bool rd) -> __amdgpu_buffer_rsrc_t {
+    const uint16_t* p = row_at(rd ? rr : 0, ver);
     if constexpr (PH) {
-      const int ph = (int)(((uintptr_t)p >> 1) & 7);
-      return row_rsrc(p - ph, rd ? ((ph + a.V + 7) >> 3) * 16 : 0);
+      const RowSplit sp = split_row(p, a.V);
+      return row_rsrc(p + sp.lead, rd ? sp.nfull * 16 : 0);
     } else {
       return row_rsrc(p, rd ? a.V * 2 : 0);
     }
   };
-  auto reads = [&](int64_t rr) -> bool {
-    if (!loss_mode) return true;
-    if (a.mask != nullptr && uload_u8(a.mask + rr) == 0) return false;
-    const int64_t yy = uload(a.ids + rr);
-    return yy >= 0 && yy < a.V;
+  auto load_edge = [&](int64_t rr, int32_t ver, bool rd) -> uint16_t {
+    if constexpr (PH) return edge_entry(row_at(rd ? rr : 0, ver), a.V, rd);
+    else return 0;
   };
   uint32_t r[NC][4];
+  uint16_t xe = 0;
   StatCount sc;
   int64_t row = blockIdx.x;
   if (a.T >= 4 * (int64_t)gridDim.x) {      // staggered starts, as in rows_bf16_resident
@@ -809,11 +837,13 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
   }
   // the call's scale (token-mean: from the valid-token count, fixed while the kernel runs)
   const float scale = loss_mode ? row_scale(a) : 1.0f;
-  bool rd_cur = row < a.T && reads(row);
+  RowMeta mc = meta_load(row), mn = meta_load(row + gridDim.x);
+  bool rd_cur = row < a.T && meta_reads(row, mc);
   {
-    const __amdgpu_buffer_rsrc_t rz = load_rsrc(row, rd_cur);
+    const __amdgpu_buffer_rsrc_t rz = load_rsrc(row, mc.ver, rd_cur);
 #pragma unroll
     for (int c = 0; c < NC; ++c) load16<kAuxLast>(r[c], rz, threadIdx.x * 16, c * NT * 16);
+    xe = load_edge(row, mc.ver, rd_cur);
   }
   int parity = 0;                          // flips after each merge that ran
   for (; row < a.T; row += gridDim.x) {
@@ -821,22 +851,23 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
     const int tid = threadIdx.x;
     const int V = a.V;
     const int voff = tid * 16;
-    const int nfull = V >> 3;
+    const uint16_t* zrow = row_at(row, mc.ver);
+    const RowSplit sp = PH ? split_row(zrow, V) : RowSplit{0, V >> 3, 0};
+    const int nfull = sp.nfull;
     const int cb = nfull / NT;
     const bool lane_in = tid < nfull - cb * NT;
-    const int ph = PH ? (int)(((uintptr_t)row_ptr<uint16_t>(a, row) >> 1) & 7) : 0;
+    const uint16_t xc = xe;
     const int64_t next = row + gridDim.x;
-    const bool rd_next = next < a.T && reads(next);
-    const __amdgpu_buffer_rsrc_t rn = load_rsrc(rd_next ? next : row, rd_next);
-    const int64_t y = uload(a.ids + row);
-    const bool good = (y >= 0) && (y < V) && version_ok(a, row);
+    const bool rd_next = next < a.T && meta_reads(next, mn);
+    const __amdgpu_buffer_rsrc_t rn = load_rsrc(rd_next ? next : row, rd_next ? mn.ver : mc.ver, rd_next);
+    xe = load_edge(rd_next ? next : row, rd_next ? mn.ver : mc.ver, rd_next);
+    const int64_t y = mc.y;
+    const bool good = (y >= 0) && (y < V) && (!a.version || (mc.ver >= 0 && mc.ver < a.nver));
+    // the scalar loads of this row and of the row after the next, waited for after the merge
+    const RowMeta mf = meta_load(next + gridDim.x);
     const TokenIn tin = token_inputs(a, row, scale);
-    float zy = 0.0f;
-    if (rd_cur && good) {
-      const uintptr_t at = (uintptr_t)logits_of(a, row) + (uintptr_t)(row * a.ld + y) * 2u;
-      const uint32_t wv = uload((const uint32_t*)(at & ~(uintptr_t)3));
-      zy = (at & 2u) ? bf16_hi(wv) : bf16_lo(wv);
-    }
+    const uintptr_t at = (uintptr_t)(zrow + (good ? y : 0));
+    const uint32_t zword = uload((const uint32_t*)(at & ~(uintptr_t)3));
     float N = -INFINITY, S = 0.0f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -847,11 +878,6 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
         x[2 * k + 1] = bf16_hi(r[c][k]);
       }
       load16<kAuxLast>(r[c], rn, voff, c * NT * 16);
-      const int lo = ph - 8 * (c * NT + tid), hi = ph + V - 8 * (c * NT + tid);
-      if constexpr (PH) {                   // entries of the neighbouring rows
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = (k >= lo && k < hi) ? x[k] : -INFINITY;
-      }
       const float cm = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7]));
       float nc = __builtin_ceilf(cm * kLog2e);
       const float sh = (nc == -INFINITY) ? 0.0f : nc;
@@ -861,7 +887,7 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) e[j] = exp2_hw(__builtin_fmaf(x[j], kLog2e, -sh));
       const float sc = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-      const bool dead = PH ? hi <= 0 : ((c > cb) || (c == cb && !lane_in));
+      const bool dead = (c > cb) || (c == cb && !lane_in);
       merge_ns_int(N, S, dead ? -INFINITY : nc, dead ? 0.0f : sc);
       // Pin the chunk's work here: otherwise the exponentials are sunk past the later
       // chunks and every chunk's unpacked values stay live at once.
@@ -869,18 +895,22 @@ __device__ __forceinline__ void fwd_rows(const RowArgsV& a) {
       __builtin_amdgcn_sched_barrier(0);
     }
     if (rd_cur) {
+      if constexpr (PH) merge_edge(N, S, tid < sp.nedge, xc);
       block_merge_ns_int<NT>(N, S, red[parity]);
       parity ^= 1;
       const float lse2 = (N == -INFINITY) ? __builtin_nanf("") : N + log2f(S);
+      const float zy = !good ? 0.0f : ((at & 2u) ? bf16_hi(zword) : bf16_lo(zword));
       finish_row(a, row, zy, lse2, good, &bc, tin, sc);
     } else if (tid == 0) {                  // masked row, or a bad id on a valid loss row
-      const bool valid = a.mask == nullptr || uload_u8(a.mask + row) != 0;
+      const bool valid = meta_valid(row, mc);
       a.lp_out[row] = valid ? __builtin_nanf("") : 0.0f;
       a.loss_tok[row] = 0.0f;
       if (a.flags) a.flags[row] = valid ? (uint8_t)(DPPO_FLAG_VALID | DPPO_FLAG_BAD_ID) : (uint8_t)0;
       if (valid) sc.bad += 1;
     }
     rd_cur = rd_next;
+    mc = mn;
+    mn = mf;
   }
   if (threadIdx.x == 0) flush_stats(a, sc);
 }
