@@ -24,6 +24,10 @@ constexpr int LMH_STAGES = 2;
 // of a tile's columns).
 constexpr int LMH_GROUP = 128;
 
+// The small tiles: 128 x 128, for launches whose large tiles would leave CUs without one, or
+// tiles mostly outside the matrix.
+constexpr int LMH_SMALL = 128;
+
 struct LmhArgs {
   const uint16_t* hidden;  // [T, d] bf16, rows contiguous
   const uint16_t* weight;  // [V, d] bf16 (LM head, [out, in] layout)
@@ -65,11 +69,14 @@ struct GemmArgs {
   int32_t accumulate;      // 1: C += A B^T; 0: C = A B^T
   float* part;             // scratch for partial products over slices of K, or NULL; as the
   int64_t part_floats;     // launcher needs it ([splits, M, N] contiguous, ldc == N)
-  int32_t tiles_m, tiles_n;  // set by the launcher
-  int32_t splits, kper;      // set by the launcher: slices of K, and K per slice
+  int32_t tiles_m, tiles_n;  // set by the launcher, as are
+  int32_t splits, kper;      // slices of K, and K per slice
 };
 constexpr int LMH_GBM = 256, LMH_GBN = 256;  // C tile of one workgroup
 
+// Whether logit tiles of a [T, n] block (K = d) run as small tiles: where that is estimated
+// faster on the current device.
+bool lmh_small_tiles(int64_t T, int64_t n, int64_t d);
 hipError_t launch_lmh_fwd_tiles(const LmhArgs& m, hipStream_t st);
 // count: add the counters to a.stats with atomics (else the loss sum derives them from flags)
 hipError_t launch_lmh_tokens(const RowArgs& a, const LmhArgs& m, bool count, hipStream_t st);

@@ -52,16 +52,30 @@ namespace {
 //  * K is padded to whole turns of the ring; stages past d load zeros (the out-of-range
 //    offset) and add nothing, which keeps the loop free of branches.
 // After the K loop, epi(acc, scratch) runs on the accumulators, with the ring as scratch.
-constexpr int kWaves = LMH_WM * LMH_WN;
+template <int WM_, int WN_, int TM_, int TN_>
+struct Tile {
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;   // waves, 32 x 32 tiles per wave
+  static constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
+  static constexpr int kWaves = WM * WN;
+  static constexpr int kIA = BM / 8 / kWaves;     // 1 KB loads per wave and stage, A
+  static constexpr int kIB = BN / 8 / kWaves;     // and B
+  static constexpr int kAEl = BM * LMH_BK;        // bf16 elements of the A tile (B follows)
+  static constexpr int kStageEl = (BM + BN) * LMH_BK;
+  static_assert(BM % (8 * kWaves) == 0 && BN % (8 * kWaves) == 0, "tile shape");
+  static_assert((LMH_STAGES - 2) * (kIA + kIB) <= 63, "ring depth");
+  static_assert(kWaves * 64 == LMH_THREADS, "workgroup size");
+  static_assert(TN * 32 == LMH_GROUP, "a wave's columns form one group");
+};
+using Large = Tile<LMH_WM, LMH_WN, LMH_TM, LMH_TN>;
+// One wave's group of 128 vocabulary rows by 32 tokens. 64 KB of LDS and 64 accumulation
+// registers a lane: two workgroups share a CU, and one computes while the other waits or runs
+// its epilogue.
+using Small = Tile<4, 1, 1, 4>;
+static_assert(Large::BM == LMH_BM && Large::BN == LMH_BN && Small::BM == LMH_SMALL &&
+              Small::BN == LMH_SMALL, "tiles");
 constexpr int kChunks = LMH_BK / 8;             // 16-byte chunks per staged row
 constexpr int kRL = 64 / kChunks;               // rows covered by one wave-wide load
-constexpr int kIA = LMH_BM / kRL / kWaves;      // loads per wave and stage, A
-constexpr int kIB = LMH_BN / kRL / kWaves;      // and B
-constexpr int kAEl = LMH_BM * LMH_BK;           // bf16 elements of the A tile (B follows)
-constexpr int kStageEl = (LMH_BM + LMH_BN) * LMH_BK;
-static_assert(LMH_BK == 64 && LMH_BM % (kRL * kWaves) == 0 && LMH_BN % (kRL * kWaves) == 0,
-              "tile shape");
-static_assert(LMH_STAGES >= 2 && (LMH_STAGES - 2) * (kIA + kIB) <= 63, "ring depth");
+static_assert(LMH_BK == 64 && LMH_STAGES >= 2, "stage");
 static_assert((LMH_BK / 16) % 2 == 0, "an even number of K steps per stage");
 
 // Swizzled position of 16-byte chunk c in staged row r.
@@ -69,21 +83,25 @@ __device__ __forceinline__ int lmh_sw(int r) { return (r >> 1) & 7; }
 
 template <int N> using IC = std::integral_constant<int, N>;
 
-template <typename Epi>
+template <typename S_, typename Epi>
 __device__ __forceinline__ void lmh_engine(const LmhArgs& m, int m0, int r0,
                                            uint16_t* (&st)[LMH_STAGES], Epi&& epi) {
-  constexpr int TM = LMH_TM, TN = LMH_TN, BK = LMH_BK, KS = BK / 16, S = LMH_STAGES;
+  constexpr int TM = S_::TM, TN = S_::TN, BK = LMH_BK, KS = BK / 16, S = LMH_STAGES;
+  constexpr int kIA = S_::kIA, kIB = S_::kIB, kAEl = S_::kAEl;
   constexpr int L = kIA + kIB;                  // loads per wave and stage
   constexpr int NF = TM + TN;                   // fragment reads per K step
   constexpr int NM = TM * TN;                   // MFMAs per K step
   constexpr int LPM = (L + NM - 1) / NM;        // refill loads per MFMA
+  constexpr int RPM = (NF + NM - 1) / NM;       // fragment reads per MFMA
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wm = wave / LMH_WN, wn = wave % LMH_WN;
+  const int wm = wave / S_::WN, wn = wave % S_::WN;
   const int d = m.d;
-  const int rows_a = min(LMH_BM, m.T - m0);
-  const int rows_b = min(LMH_BN, m.V - r0);
+  const int rows_a = min(S_::BM, m.T - m0);
+  // a small tile may lie past V (an empty resource); a scalar by hand, so that the resource stays
+  // in scalar registers and its loads need no loop over its values
+  const int rows_b = __builtin_amdgcn_readfirstlane(max(0, min(S_::BN, m.V - r0)));
   const __amdgpu_buffer_rsrc_t ra = row_rsrc(m.hidden + (int64_t)m0 * d, rows_a * d * 2);
   const __amdgpu_buffer_rsrc_t rb = row_rsrc(m.weight + (int64_t)r0 * d, rows_b * d * 2);
 
@@ -157,7 +175,10 @@ __device__ __forceinline__ void lmh_engine(const LmhArgs& m, int m0, int r0,
     constexpr bool loads = decltype(LOADS)::value;
     auto one = [&](auto I) {
       constexpr int i = decltype(I)::value;
-      if constexpr (i < NF) read_one(rs, rks, IC<f ^ 1>{}, IC<i>{});
+      [&]<int... vs>(std::integer_sequence<int, vs...>) {
+        ((i * RPM + vs < NF ? read_one(rs, rks, IC<f ^ 1>{}, IC<(i * RPM + vs < NF ? i * RPM + vs : 0)>{})
+                            : void()), ...);
+      }(std::make_integer_sequence<int, RPM>{});
       if constexpr (loads) {
         [&]<int... vs>(std::integer_sequence<int, vs...>) {
           ((i * LPM + vs < L ? load_one(dst, kb, IC<(i * LPM + vs < L ? i * LPM + vs : 0)>{})
@@ -223,24 +244,25 @@ __device__ __forceinline__ void lmh_engine(const LmhArgs& m, int m0, int r0,
 // and vocabulary row
 //   r0 + wn 32 TN + ni 32 + 8 (r / 4) + 4 (l / 32) + r % 4,
 // so a lane sees one token per mi and, for each (ni, r / 4), four consecutive vocabulary rows.
+template <typename S_>
 struct LmhLane {
   int wm, wn, lane;
-  __device__ LmhLane() : wm((threadIdx.x >> 6) / LMH_WN), wn((threadIdx.x >> 6) % LMH_WN), lane(threadIdx.x & 63) {}
-  __device__ int token(int m0, int mi) const { return m0 + wm * 32 * LMH_TM + mi * 32 + (lane & 31); }
+  __device__ LmhLane() : wm((threadIdx.x >> 6) / S_::WN), wn((threadIdx.x >> 6) % S_::WN), lane(threadIdx.x & 63) {}
+  __device__ int token(int m0, int mi) const { return m0 + wm * 32 * S_::TM + mi * 32 + (lane & 31); }
   // tile-relative vocabulary row of register r of tile ni
   __device__ int vrow(int ni, int r) const {
-    return wn * 32 * LMH_TN + ni * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    return wn * 32 * S_::TN + ni * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
   }
 };
 
 }  // namespace
 
-#define LMH_RUN_ENGINE(m, m0, r0, epi)                                                    \
+#define LMH_RUN_ENGINE(S_, m, m0, r0, epi)                                                \
   do {                                                                                    \
-    __shared__ __align__(16) uint16_t lmh_st[LMH_STAGES][kStageEl];                       \
+    __shared__ __align__(16) uint16_t lmh_st[LMH_STAGES][S_::kStageEl];                   \
     uint16_t* ring[LMH_STAGES];                                                           \
     _Pragma("unroll") for (int i = 0; i < LMH_STAGES; ++i) ring[i] = lmh_st[i];            \
-    lmh_engine(m, m0, r0, ring, epi);                                                     \
+    lmh_engine<S_>(m, m0, r0, ring, epi);                                                   \
   } while (0)
 
 // Forward: per-token partial log-sum-exp (log2 domain) of each 128-entry vocabulary group of
@@ -253,23 +275,23 @@ struct LmhLane {
 // rows drops the stores of rows past T.
 // An entry of z that is NaN or +inf makes the partial sum NaN; a group of only -inf logits
 // contributes nothing.
+template <typename S_>
 __global__ __launch_bounds__(LMH_THREADS) void lmh_fwd_tiles(LmhArgs m) {
-  const int m0 = blockIdx.x * LMH_BM;
+  const int m0 = blockIdx.x * S_::BM;
   const int nt = blockIdx.y;
-  const int r0 = m.n0 + nt * LMH_BN;
-  const int ncols = min(LMH_BN, m.n1 - r0);
-  auto epi = [&](f32x16 (&acc)[LMH_TM][LMH_TN], float*) {
-    const LmhLane L;
-    const bool ragged = ncols < LMH_BN;       // only the last vocabulary tile
+  const int r0 = m.n0 + nt * S_::BN;
+  const int ncols = min(S_::BN, m.n1 - r0);   // not positive in a small tile past V (no group there)
+  auto epi = [&](f32x16 (&acc)[S_::TM][S_::TN], float*) {
+    const LmhLane<S_> L;
+    const bool ragged = ncols < S_::BN;       // only the last vocabulary tile
     const int grp = (r0 / LMH_GROUP) + L.wn;  // this wave's 128 columns
-    const int prows = m.store_p ? min(LMH_BM, m.T - m0) : 0;
+    const int prows = m.store_p ? min(S_::BM, m.T - m0) : 0;
     const __amdgpu_buffer_rsrc_t rp = row_rsrc(m.g + (int64_t)m0 * m.ldg, (int)(prows * m.ldg * 2));
-    static_assert(LMH_TN * 32 == LMH_GROUP, "a wave's columns form one group");
 #pragma unroll
-    for (int mi = 0; mi < LMH_TM; ++mi) {
+    for (int mi = 0; mi < S_::TM; ++mi) {
       float mx = -INFINITY;
 #pragma unroll
-      for (int ni = 0; ni < LMH_TN; ++ni)
+      for (int ni = 0; ni < S_::TN; ++ni)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float x = acc[mi][ni][r];
@@ -282,7 +304,7 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_fwd_tiles(LmhArgs m) {
       const int poff = (int)(((int64_t)(t - m0) * m.ldg + r0) * 2);
       float sum = 0.0f;
 #pragma unroll
-      for (int ni = 0; ni < LMH_TN; ++ni)
+      for (int ni = 0; ni < S_::TN; ++ni)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int v0 = L.vrow(ni, 4 * q);
@@ -307,7 +329,7 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_fwd_tiles(LmhArgs m) {
       }
     }
   };
-  LMH_RUN_ENGINE(m, m0, r0, epi);
+  LMH_RUN_ENGINE(S_, m, m0, r0, epi);
 }
 
 // One wave per token: merges the token's group partials into lse2, forms z[t, y_t] as a dot
@@ -440,14 +462,15 @@ __global__ __launch_bounds__(256) void lmh_grad_scale(LmhArgs m, int per_row) {
 // for the tile's rows of the chunk [n0, n1); tokens that were not evaluated get zeros. The
 // last tile also zeroes the entries past the chunk up to the next multiple of 8, which the
 // gradient products read as whole 16-byte chunks.
+template <typename S_>
 __global__ __launch_bounds__(LMH_THREADS) void lmh_bwd_tiles(LmhArgs m) {
-  const int m0 = blockIdx.x * LMH_BM;
-  const int r0 = m.n0 + blockIdx.y * LMH_BN;
-  const int ncols = min(LMH_BN, m.n1 - r0);
-  auto epi = [&](f32x16 (&acc)[LMH_TM][LMH_TN], float*) {
-    const LmhLane L;
+  const int m0 = blockIdx.x * S_::BM;
+  const int r0 = m.n0 + blockIdx.y * S_::BN;
+  const int ncols = min(S_::BN, m.n1 - r0);
+  auto epi = [&](f32x16 (&acc)[S_::TM][S_::TN], float*) {
+    const LmhLane<S_> L;
 #pragma unroll
-    for (int mi = 0; mi < LMH_TM; ++mi) {
+    for (int mi = 0; mi < S_::TM; ++mi) {
       const int t = L.token(m0, mi);
       if (t >= m.T) continue;
       const bool ev = m.ev[t] != 0;
@@ -456,7 +479,7 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_bwd_tiles(LmhArgs m) {
       const int64_t yr = m.ids[t] - r0;        // the token's id relative to the tile
       uint16_t* grow = m.g + (int64_t)t * m.ldg + (r0 - m.n0);
 #pragma unroll
-      for (int ni = 0; ni < LMH_TN; ++ni)
+      for (int ni = 0; ni < S_::TN; ++ni)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           // four consecutive vocabulary rows v0 .. v0 + 3 of this token
@@ -480,12 +503,19 @@ __global__ __launch_bounds__(LMH_THREADS) void lmh_bwd_tiles(LmhArgs m) {
         }
     }
   };
-  LMH_RUN_ENGINE(m, m0, r0, epi);
+  LMH_RUN_ENGINE(S_, m, m0, r0, epi);
 }
 
 hipError_t launch_lmh_fwd_tiles(const LmhArgs& m, hipStream_t st) {
-  const dim3 grid((m.T + LMH_BM - 1) / LMH_BM, lmh_tiles(m.n1 - m.n0));
-  lmh_fwd_tiles<<<grid, LMH_THREADS, 0, st>>>(m);
+  const int n = m.n1 - m.n0;
+  if (lmh_small_tiles(m.T, n, m.d)) {
+    // every group has its tile, the one past V too (it stores the empty partial)
+    const dim3 grid((m.T + Small::BM - 1) / Small::BM, lmh_groups(n));
+    lmh_fwd_tiles<Small><<<grid, LMH_THREADS, 0, st>>>(m);
+  } else {
+    const dim3 grid((m.T + LMH_BM - 1) / LMH_BM, lmh_tiles(n));
+    lmh_fwd_tiles<Large><<<grid, LMH_THREADS, 0, st>>>(m);
+  }
   return hipGetLastError();
 }
 
@@ -508,8 +538,14 @@ hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st) {
 }
 
 hipError_t launch_lmh_bwd_tiles(const LmhArgs& m, hipStream_t st) {
-  const dim3 grid((m.T + LMH_BM - 1) / LMH_BM, lmh_tiles(m.n1 - m.n0));
-  lmh_bwd_tiles<<<grid, LMH_THREADS, 0, st>>>(m);
+  const int n = m.n1 - m.n0;
+  if (lmh_small_tiles(m.T, n, m.d)) {
+    const dim3 grid((m.T + Small::BM - 1) / Small::BM, (n + Small::BN - 1) / Small::BN);
+    lmh_bwd_tiles<Small><<<grid, LMH_THREADS, 0, st>>>(m);
+  } else {
+    const dim3 grid((m.T + LMH_BM - 1) / LMH_BM, lmh_tiles(n));
+    lmh_bwd_tiles<Large><<<grid, LMH_THREADS, 0, st>>>(m);
+  }
   return hipGetLastError();
 }
 

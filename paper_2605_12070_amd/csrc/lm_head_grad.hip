@@ -43,6 +43,7 @@
 // launch (T = 8192, d = 4096, V = 151936) at the same speed: the products are not bound by
 // L2 misses.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -60,9 +61,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int GW_M = 2, GW_N = 2;                // waves
-constexpr int GTM = 4, GTN = 4;                  // 32 x 32 tiles per wave
-constexpr int GBM = 32 * GW_M * GTM;             // 256
-constexpr int GBN = 32 * GW_N * GTN;             // 256
 #ifndef LMG_BK
 #define LMG_BK 32
 #endif
@@ -72,11 +70,20 @@ constexpr int GBN = 32 * GW_N * GTN;             // 256
 constexpr int GBK = LMG_BK;                      // K per LDS stage
 constexpr int GTHREADS = 64 * GW_M * GW_N;
 constexpr int GS = LMG_STAGES;                   // LDS stages
-constexpr int kOpEl = 256 * GBK;                 // bf16 elements of one operand tile
-constexpr int kLoads = kOpEl * 2 / 1024 / (GW_M * GW_N);  // wave loads per operand, stage
 constexpr int kC = GBK / 8;                      // 16-byte chunks per K-major staged row
 constexpr int kRL = 64 / kC;                     // K-major rows per wave load
-static_assert(GBM == LMH_GBM && GBN == LMH_GBN && (GBK == 64 || GBK == 32), "tile shape");
+static_assert(GW_M == 2 && GW_N == 2 && (GBK == 64 || GBK == 32), "tile shape");
+
+// A workgroup's square C tile: G x G matrix-core tiles of 32 x 32 per wave. G = 4 is 256 x 256,
+// one workgroup per CU. G = 2 is 128 x 128: twice the operand bytes per flop, but 64 KB of LDS
+// and 64 accumulation registers a lane, so two workgroups share a CU.
+template <int G>
+struct Sq {
+  static constexpr int W = 64 * G;               // C rows and columns of a workgroup
+  static constexpr int kOpEl = W * GBK;          // bf16 elements of one operand tile
+  static constexpr int kLoads = kOpEl * 2 / 1024 / (GW_M * GW_N);  // wave loads per operand, stage
+};
+static_assert(Sq<4>::W == LMH_GBM && LMH_GBM == LMH_GBN && Sq<2>::W == LMH_SMALL, "tiles");
 
 template <int N> using IC = std::integral_constant<int, N>;
 
@@ -87,8 +94,10 @@ __device__ __forceinline__ int sw_mn(int r) { return (r & 3) << 2; }  // MN-majo
 constexpr int kOob = 0x7fffff00;  // an offset past every resource: the load returns zeros
 
 // One operand of a product as the engine loads it.
-template <bool MN>
+template <bool MN, int G>
 struct Operand {
+  static constexpr int W = Sq<G>::W, kLoads = Sq<G>::kLoads;
+  static constexpr int kRowL = W / 8;  // lanes of a load per MN-major staged row
   const uint16_t* p;   // bf16
   int64_t ld;          // row stride, elements
   int32_t ext;         // K-major: rows of the matrix (its M or N extent);
@@ -107,7 +116,7 @@ struct Operand {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if constexpr (!MN) {
       // load i: tile rows kRL (wave kLoads + i) .. +kRL-1; lane -> row l / kC, position l % kC
-      const int rows = min(256, ext - o0);
+      const int rows = min(W, ext - o0);
       rs = row_rsrc(p + (int64_t)o0 * ld, rows > 0 ? (int)(rows * ld * 2) : 0);
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
@@ -115,11 +124,11 @@ struct Operand {
         off[i] = (int)(row * ld * 2) + (((lane % kC) ^ sw_k(row)) * 16);
       }
     } else {
-      // load i: staged rows (K) 2 (wave kLoads + i), +1; lane -> row l / 32, position l % 32
+      // load i: 64 / kRowL staged rows (K); lane -> row l / kRowL, position l % kRowL
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int row = 2 * (wave * kLoads + i) + (lane >> 5);
-        const int c = (lane & 31) ^ sw_mn(row);
+        const int row = 64 / kRowL * (wave * kLoads + i) + lane / kRowL;
+        const int c = (lane % kRowL) ^ sw_mn(row);
         off[i] = (o0 + 8 * c < ext) ? (int)(row * ld * 2) + c * 16 : kOob;
       }
     }
@@ -158,25 +167,25 @@ struct Operand {
   }
 };
 
-// Fragment reads of one operand for the wave's four 32-row tiles at tile offset wo (0 or
-// 128). K-major: one 16-byte read per fragment. MN-major: two transposing 8-byte reads,
+// Fragment reads of one operand for the wave's G 32-row tiles at tile offset wo (0 or 32 G). K-major: one 16-byte read per fragment. MN-major: two transposing 8-byte reads,
 // K 0..3 and 4..7 of the lane's eight.
-template <bool MN>
+template <bool MN, int G>
 struct Frags {
-  int base[4];  // per-fragment lane byte offsets into an operand tile
+  static constexpr int kRowB = Sq<G>::W * 2;  // bytes of an MN-major staged row
+  int base[G];  // per-fragment lane byte offsets into an operand tile
 
   __device__ __forceinline__ void init(int wo) {
     const int lane = threadIdx.x & 63;
     if constexpr (!MN) {
       const int row = wo + (lane & 31);
 #pragma unroll
-      for (int f = 0; f < 4; ++f) base[f] = (row + 32 * f) * GBK * 2;
+      for (int f = 0; f < G; ++f) base[f] = (row + 32 * f) * GBK * 2;
     } else {
       const int b = lane >> 4, s = lane & 15, q = s >> 2, e = s & 3;
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        const int pos = 4 * ((wo >> 5) + (f ^ q)) + 2 * (b & 1) + (e >> 1);
-        base[f] = (8 * (b >> 1) + q) * 512 + pos * 16 + (e & 1) * 8;
+      for (int f = 0; f < G; ++f) {
+        const int pos = 4 * (((wo >> 5) + f) ^ q) + 2 * (b & 1) + (e >> 1);
+        base[f] = (8 * (b >> 1) + q) * kRowB + pos * 16 + (e & 1) * 8;
       }
     }
   }
@@ -190,7 +199,7 @@ struct Frags {
       const int col = ((2 * ks + (lane >> 5)) ^ sw_k(lane & 31)) * 16;
       out = *(const u32x4*)(tb + base[F] + col);
     } else {
-      auto* pp = (__attribute__((address_space(3))) s16x4*)(tb + base[F] + ks * 8192 + H * 2048);
+      auto* pp = (__attribute__((address_space(3))) s16x4*)(tb + base[F] + ks * 16 * kRowB + H * 4 * kRowB);
       const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(pp));
       if constexpr (H == 0) {
         out.x = v.x;
@@ -211,25 +220,27 @@ struct Ring {
   uint16_t* b[GS];
 };
 
-template <bool AMN, bool BMN, typename Epi>
+template <bool AMN, bool BMN, int G, typename Epi>
 __device__ __forceinline__ void grad_engine(const GemmArgs& g, int m0, int n0, const Ring& ring,
                                             Epi&& epi) {
+  constexpr int GTM = G, GTN = G, kLoads = Sq<G>::kLoads;
   constexpr int RA = AMN ? 2 : 1, RB = BMN ? 2 : 1;   // reads per fragment
   constexpr int NR = GTM * RA + GTN * RB;              // fragment reads per K step
   constexpr int NM = GTM * GTN;                         // MFMAs per K step
   constexpr int L = 2 * kLoads;                         // refill loads per stage and wave
   constexpr int KS = GBK / 16;                          // K steps per stage
-  static_assert(NR <= NM && L <= NM && KS % 2 == 0, "schedule");
+  constexpr int RPM = (NR + NM - 1) / NM;               // reads per MFMA
+  static_assert(L <= NM && KS % 2 == 0, "schedule");
   const int wave = threadIdx.x >> 6;
   const int wm = wave / GW_N, wn = wave % GW_N;
-  Operand<AMN> A;
-  Operand<BMN> B;
+  Operand<AMN, G> A;
+  Operand<BMN, G> B;
   A.init(g.a, g.lda, g.a_ext, g.K, m0);
   B.init(g.b, g.ldb, g.b_ext, g.K, n0);
-  Frags<AMN> FA;
-  Frags<BMN> FB;
-  FA.init(wm * 128);
-  FB.init(wn * 128);
+  Frags<AMN, G> FA;
+  Frags<BMN, G> FB;
+  FA.init(wm * 32 * G);
+  FB.init(wn * 32 * G);
 
   f32x16g acc[GTM][GTN];
 #pragma unroll
@@ -242,8 +253,8 @@ __device__ __forceinline__ void grad_engine(const GemmArgs& g, int m0, int n0, c
 
   // read op I of K step ks of slot s into set S_, in the order the next step's MFMAs first
   // use the fragments (MFMA i takes A fragment i / GTN and B fragment i % GTN): A 0, then
-  // B 0 .. GTN - 1, then A 1 .. GTM - 1. Read I is issued after MFMA I of this step, so
-  // every fragment has at least 8 MFMAs to arrive.
+  // B 0 .. GTN - 1, then A 1 .. GTM - 1. Read I is issued before MFMA I of this step (I / RPM
+  // for the small tile), so every fragment of the large tile has at least 8 MFMAs to arrive.
   auto read_one = [&](auto J, int ks, auto S_, auto I) {
     constexpr int j0 = decltype(J)::value, f = decltype(S_)::value, i = decltype(I)::value;
     if constexpr (i < RA) {
@@ -276,7 +287,10 @@ __device__ __forceinline__ void grad_engine(const GemmArgs& g, int m0, int n0, c
     constexpr bool loads = decltype(LOADS)::value;
     auto one = [&](auto I) {
       constexpr int i = decltype(I)::value;
-      if constexpr (i < NR) read_one(RS, rks, IC<f ^ 1>{}, IC<i>{});
+      [&]<int... vs>(std::integer_sequence<int, vs...>) {
+        ((i * RPM + vs < NR ? read_one(RS, rks, IC<f ^ 1>{}, IC<(i * RPM + vs < NR ? i * RPM + vs : 0)>{})
+                            : void()), ...);
+      }(std::make_integer_sequence<int, RPM>{});
       if constexpr (loads && i < L) load_one(DST, kb, ra, rb, IC<i>{});
       mfma_one(IC<f>{}, IC<i>{});
       __builtin_amdgcn_sched_barrier(0);
@@ -358,8 +372,9 @@ __device__ __forceinline__ void grouped_tile(int L, int tiles_m, int tiles_n, in
 // SPLIT the workgroup takes one slice of K and stores its partial product (cached: the sum
 // kernel reads it next) into slice s of g.part. (As a run-time branch in one kernel the slice
 // arithmetic made the unsliced products 5 % slower.)
-template <bool AMN, bool BMN, bool SPLIT>
+template <bool AMN, bool BMN, bool SPLIT, int G>
 __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
+  constexpr int GTM = G, GTN = G, GBM = Sq<G>::W, GBN = Sq<G>::W, kOpEl = Sq<G>::kOpEl;
   // one LDS object per slot and operand (a 2-D array is one object: the transposing reads of
   // one slot would then wait for the loads into another); unused ones are not allocated
   static_assert(GS >= 2 && GS <= 5, "LDS slots");
@@ -376,7 +391,9 @@ __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
   const int nt = g.tiles_m * g.tiles_n;
   int L = xcd_tile(blockIdx.x, SPLIT ? nt * g.splits : nt);
   if constexpr (SPLIT) {
-    const int s = L / nt;
+    // made a scalar by hand: otherwise the resources built from it sat in vector registers, and
+    // every load of the K loop ran in a loop over their values (a stage 1.05 us against 0.86)
+    const int s = __builtin_amdgcn_readfirstlane(L / nt);
     L -= s * nt;
     const int64_t k0 = (int64_t)s * g.kper;
     g.a += AMN ? k0 * g.lda : k0;
@@ -390,8 +407,8 @@ __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
   const int n0 = tn * GBN;
   auto epi = [&](f32x16g (&acc)[GTM][GTN], int wm, int wn) {
     const int lane = threadIdx.x & 63;
-    const int n_l = n0 + wn * 128 + (lane & 31);
-    const int m_l = m0 + wm * 128 + 4 * (lane >> 5);
+    const int n_l = n0 + wn * 32 * G + (lane & 31);
+    const int m_l = m0 + wm * 32 * G + 4 * (lane >> 5);
 #pragma unroll
     for (int mi = 0; mi < GTM; ++mi)
 #pragma unroll
@@ -413,7 +430,7 @@ __global__ __launch_bounds__(GTHREADS) void lmh_grad_gemm(GemmArgs g) {
         }
       }
   };
-  grad_engine<AMN, BMN>(g, m0, n0, ring, epi);
+  grad_engine<AMN, BMN, G>(g, m0, n0, ring, epi);
 }
 
 // C (+)= the sum of the slices' partial products, in slice order (the same bits every run).
@@ -434,16 +451,45 @@ namespace {
 constexpr int kTurn = GS * GBK;     // K of one turn of the LDS ring: a slice is whole turns
 constexpr int kMaxSplits = 128;
 
-// Estimated time of a product in microseconds, splits slices of kper K over cus CUs (one
-// workgroup per CU): the constants are those of the full chip at K in the thousands (a
-// 32-deep stage of every CU's tile 0.86 us) and a tile's fixed part (prologue, epilogue); the
-// slices' sum reads and writes at 4 TB/s and costs a launch.
-double gemm_us(int64_t tiles, int64_t splits, int64_t kper, int64_t mn, int cus) {
-  const double waves = (double)((tiles * splits + cus - 1) / cus);
-  const double stages = (double)((kper + kTurn - 1) / kTurn * GS);
-  double t = waves * (0.86 * stages * (GBK / 32) + 8.0);
-  if (splits > 1) t += 5.0 + (double)(splits + 1) * (double)mn * 4.0 / 4.0e6;
+// Estimated time in microseconds of n C tiles with `stages` 32-deep stages of K each, on cus CUs.
+// Large tiles run one to a CU: 0.86 us a stage with every CU busy, then `fixed` for prologue and
+// epilogue (not overlapped). Small tiles run two to a CU, `pair` a stage for both together, or
+// one alone at `single`, and `part` for what does not overlap. Past four rounds the last one is
+// not waited for as a whole: CUs take tiles as they finish. Fitted to the times of both sizes at
+// T = 128 .. 8192, d = 512 .. 4096, V = 2000 .. 151936, for example (large, small, us): logits T = 292,
+// d = 1256, V = 65584 149, 110; T = 5962, d = 1376, V = 9404 218, 271; dhidden T = 4068, d = 584,
+// V = 2328 73, 32; T = 1024, d = 2048, V = 32000 150, 165; dweight T = 4068 98, 41; T = 128, d = 4096,
+// V = 50257 282, 205; T = 5962 171, 199.
+struct TileCost {
+  double fixed, pair, single, part;
+};
+double tiles_us(int64_t n, double stages, bool small, const TileCost& c, int cus) {
+  const double r = (double)n / cus;
+  if (!small) return (r <= 4.0 ? std::ceil(r) : r + 0.3) * (0.86 * stages + c.fixed);
+  const double q = r <= 4.0 ? std::ceil(r) : r + 0.3;   // tiles of the busiest CU
+  const double pairs = q <= 4.0 ? std::floor(q / 2.0) : q / 2.0;
+  return pairs * (c.pair * stages + c.part) + (q - 2.0 * pairs) * (c.single * stages + c.part);
+}
+
+// A gradient product [M, N] over K in splits slices of kper. The large tiles' epilogue is bound by
+// the writes of all CUs together; the slices' sum reads and writes at 6 TB/s and costs a launch.
+double gemm_us(int64_t M, int64_t N, int64_t splits, int64_t kper, bool a_mn, bool small, int cus) {
+  const int64_t w = small ? LMH_SMALL : LMH_GBM;
+  const int64_t n = ((M + w - 1) / w) * ((N + w - 1) / w) * splits;
+  const double stages = (double)((kper + kTurn - 1) / kTurn * GS) * (GBK / 32);
+  const TileCost c = {4.0 + 12.0 * std::min(1.0, (double)n / cus), a_mn ? 0.48 : 0.60, a_mn ? 0.28 : 0.33,
+                      a_mn ? 5.0 : 7.0};
+  double t = tiles_us(n, stages, small, c, cus);
+  if (splits > 1) t += 3.0 + (double)(splits + 1) * (double)(M * N) * 4.0 / 6.0e6;
   return t;
+}
+
+// The logit tiles of a [T, n] block, K = d.
+double logits_us(int64_t T, int64_t n, int64_t d, bool small, int cus) {
+  const int64_t w = small ? LMH_SMALL : LMH_BM;
+  constexpr int64_t turn = LMH_STAGES * LMH_BK;
+  const double stages = (double)((d + turn - 1) / turn * (turn / 32));
+  return tiles_us(((T + w - 1) / w) * ((n + w - 1) / w), stages, small, {17.0, 0.58, 0.38, 7.0}, cus);
 }
 
 int cu_count() {
@@ -456,36 +502,42 @@ int cu_count() {
 
 }  // namespace
 
-// The product in splits slices of K where that is estimated faster: with few C tiles and a
-// long K (dhidden of a short batch: K is the vocabulary) most CUs would have no tile at all.
-static void lmh_pick_splits(GemmArgs& g, int cus) {
-  g.splits = 1;
-  g.kper = g.K;
-  if (!g.part || g.ldc != g.N || g.N % 4 != 0) return;
-  const int64_t tiles = (int64_t)((g.M + GBM - 1) / GBM) * ((g.N + GBN - 1) / GBN);
+bool lmh_small_tiles(int64_t T, int64_t n, int64_t d) {
+  const int cus = cu_count();
+  return logits_us(T, n, d, true, cus) < logits_us(T, n, d, false, cus);
+}
+
+// The tile size, and the product in splits slices of K, where estimated fastest: with few C
+// tiles and a long K (dhidden of a short batch: K is the vocabulary) most CUs would have no
+// tile at all. Returns the estimate.
+static double lmh_pick(GemmArgs& g, bool a_mn, bool* small, int cus) {
   const int64_t mn = (int64_t)g.M * g.N;
-  double best = gemm_us(tiles, 1, g.K, mn, cus);
-  const int64_t most = std::min<int64_t>(kMaxSplits, g.part_floats / mn);
-  for (int64_t s = 2; s <= most; ++s) {
-    const int64_t kper = ((g.K + s - 1) / s + kTurn - 1) / kTurn * kTurn;
-    const int64_t used = (g.K + kper - 1) / kper;       // slices that hold any K
-    if (used != s) continue;
-    const double t = gemm_us(tiles, s, kper, mn, cus);
-    if (t < best) {
-      best = t;
-      g.splits = (int32_t)s;
-      g.kper = (int32_t)kper;
+  const bool can_split = g.part && g.ldc == g.N && g.N % 4 == 0;
+  const int64_t most = can_split ? std::min<int64_t>(kMaxSplits, g.part_floats / mn) : 1;
+  double best = 0.0;
+  g.splits = 0;
+  for (int sm = 0; sm < 2; ++sm) {
+    for (int64_t s = 1; s <= std::max<int64_t>(1, most); ++s) {
+      const int64_t kper = s == 1 ? g.K : ((g.K + s - 1) / s + kTurn - 1) / kTurn * kTurn;
+      if ((g.K + kper - 1) / kper != s) continue;         // some slice would hold no K
+      const double t = gemm_us(g.M, g.N, s, kper, a_mn, sm == 1, cus);
+      if (g.splits == 0 || t < best) {
+        best = t;
+        g.splits = (int32_t)s;
+        g.kper = (int32_t)kper;
+        *small = sm == 1;
+      }
     }
   }
+  return best;
 }
 
 int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool dhidden, bool dweight) {
   const int cus = cu_count();
-  const int64_t tm = (T + LMH_BM - 1) / LMH_BM, tn = (d + GBN - 1) / GBN;
   // one step of c vocabulary rows: the logit tiles, then the two products
   auto step_us = [&](int64_t c) {
-    const int64_t tv = (c + LMH_BN - 1) / LMH_BN;
-    double t = 15.0 + gemm_us(tm * tv, 1, d, 0, cus);
+    double t = 15.0 + std::min(logits_us(T, c, d, false, cus), logits_us(T, c, d, true, cus));
+    bool small;
     if (dhidden) {
       GemmArgs g{};
       g.M = (int32_t)T;
@@ -497,10 +549,15 @@ int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool d
         g.part = &scratch;                       // a stand-in: only its size matters here
         g.part_floats = c * d;
       }
-      lmh_pick_splits(g, cus);
-      t += gemm_us(tm * tn, g.splits, g.kper, T * d, cus);
+      t += lmh_pick(g, false, &small, cus);
     }
-    if (dweight) t += gemm_us(tv * tn, 1, T, 0, cus);
+    if (dweight) {
+      GemmArgs g{};
+      g.M = (int32_t)c;
+      g.N = (int32_t)d;
+      g.K = (int32_t)T;
+      t += lmh_pick(g, true, &small, cus);
+    }
     return t;
   };
   int64_t best_c = chunk;
@@ -517,21 +574,29 @@ int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool d
   return best_c;
 }
 
+namespace {
+template <int G>
+hipError_t launch_gemm(GemmArgs& g, bool a_mn, hipStream_t st) {
+  g.tiles_m = (g.M + Sq<G>::W - 1) / Sq<G>::W;
+  g.tiles_n = (g.N + Sq<G>::W - 1) / Sq<G>::W;
+  const int64_t nt = (int64_t)g.tiles_m * g.tiles_n * g.splits;
+  if (nt > 0x7fffffff) return hipErrorInvalidValue;
+  auto* fn = a_mn ? (g.splits > 1 ? lmh_grad_gemm<true, true, true, G> : lmh_grad_gemm<true, true, false, G>)
+                  : (g.splits > 1 ? lmh_grad_gemm<false, true, true, G> : lmh_grad_gemm<false, true, false, G>);
+  fn<<<(unsigned)nt, GTHREADS, 0, st>>>(g);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_lmh_grad_gemm(const GemmArgs& g0, bool a_mn, bool b_mn, hipStream_t st) {
   GemmArgs g = g0;
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  g.tiles_m = (g.M + GBM - 1) / GBM;
-  g.tiles_n = (g.N + GBN - 1) / GBN;
-  lmh_pick_splits(g, cu_count());
-  const int64_t nt = (int64_t)g.tiles_m * g.tiles_n * g.splits;
-  if (nt > 0x7fffffff) return hipErrorInvalidValue;
   if (!b_mn) return hipErrorInvalidValue;
-  auto* fn = a_mn ? (g.splits > 1 ? lmh_grad_gemm<true, true, true> : lmh_grad_gemm<true, true, false>)
-                  : (g.splits > 1 ? lmh_grad_gemm<false, true, true> : lmh_grad_gemm<false, true, false>);
-  fn<<<(unsigned)nt, GTHREADS, 0, st>>>(g);
+  bool small = false;
+  lmh_pick(g, a_mn, &small, cu_count());
+  const hipError_t e = small ? launch_gemm<2>(g, a_mn, st) : launch_gemm<4>(g, a_mn, st);
+  if (e != hipSuccess) return e;
   if (g.splits > 1) {
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int64_t n4 = (int64_t)g.M * g.N / 4;
     lmh_sum_slices<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>((const f32x4*)g.part, n4, g.splits,
                                                                 (f32x4*)g.c, g.accumulate);

@@ -356,3 +356,13 @@ def test_hidden_gradient_in_slices_of_the_vocabulary(T, d, V, chunk):
     # which |G| |W| bounds; |G| <= 2 |w| per row with |w| <= 2.4 |A| / n_valid
     bound = V * 2.0 ** -24 * 4.8 * wl.adv.abs().max() / max(1, int(wl.mask.sum())) * wl.weight.float().abs().max()
     assert (both - ref).abs().max() <= bound
+
+
+# Small tiles (128 x 128): their edges in T, V and d, a tile past V, with and without chunks; then
+# batches large enough for the large tiles of each of the three products, ragged in every size.
+@pytest.mark.parametrize("T,d,V,chunk", [(1, 8, 1, 0), (127, 136, 127, 0), (128, 128, 128, 0),
+                                         (129, 120, 129, 0), (257, 64, 385, 0), (300, 520, 2100, 0),
+                                         (131, 200, 1153, 256), (513, 72, 3000, 512),
+                                         (1001, 1000, 16301, 0), (4001, 3000, 300, 0)])
+def test_tile_sizes_at_their_edges(T, d, V, chunk):
+    _run(T, d, V, seed=T + d, vocab_chunk=chunk, bad_ids=(3,) if T > 8 else ())
