@@ -200,6 +200,29 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
     uint8_t* flags_out, void* dlogits, int64_t ld_dlogits, int32_t* stats_out, void* stream);
 
 /*
+ * decoupled_ppo_loss_call -- decoupled_ppo_loss_fwd_bwd with its arguments in one struct (the
+ * fields are its parameters, with the same meaning and the same checks), for callers whose
+ * foreign-function interface converts arguments one by one: from Python the 21 arguments took
+ * 4 us of a small call, the packed struct 1.5 us.
+ */
+typedef struct dppo_loss_call {
+  const void* logits;
+  int64_t dtype, T, V, ld;
+  const int64_t* token_ids;
+  const float *logp_mu_old, *logp_ref, *advantages;
+  const uint8_t* loss_mask;
+  const float* token_scale;
+  float *logp_out, *loss_tok_out, *loss_out;
+  uint8_t* flags_out;
+  void* dlogits;
+  int64_t ld_dlogits;
+  int32_t* stats_out;
+  void* stream;
+  dppo_params params;
+} dppo_loss_call;
+dppo_status decoupled_ppo_loss_call(const dppo_loss_call* call);
+
+/*
  * fused_lm_head_loss_fwd_bwd -- decoupled_ppo_loss_fwd_bwd on logits z = hidden weight^T
  * that are never written to memory, with the gradients of L for both factors:
  *     d L / d hidden = G weight,   d L / d weight = G^T hidden,

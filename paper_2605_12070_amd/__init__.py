@@ -33,7 +33,8 @@ __all__ = [
 
 
 def _stream(dev: torch.device) -> int:
-    return torch.cuda.current_stream(dev).cuda_stream
+    # the raw handle: a Stream object costs 2 us of a call
+    return torch._C._cuda_getCurrentRawStream(dev.index)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -45,11 +46,13 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _matrix(t: torch.Tensor, name: str):
-    if t.dim() != 2 or t.stride(1) != 1:
+    stride = t.stride()
+    if len(stride) != 2 or stride[1] != 1:
         raise ValueError(f"{name} must be a 2-D tensor with unit stride in its last dim")
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
-    return t.data_ptr(), t.shape[0], t.shape[1], t.stride(0)
+    T, V = t.shape
+    return t.data_ptr(), T, V, stride[0]
 
 
 def _vec(t, T, dtype, name, dev, optional=False):
@@ -57,7 +60,7 @@ def _vec(t, T, dtype, name, dev, optional=False):
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if t.dtype != dtype or t.dim() != 1 or t.shape[0] != T or not t.is_contiguous():
+    if t.dtype != dtype or t.shape != (T,) or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous [{T}] {dtype} tensor")
     if t.device != dev:
         raise ValueError(f"{name} must live on {dev}")
@@ -151,15 +154,15 @@ def decoupled_ppo_loss_fwd_bwd(logits, token_ids, logp_mu_old, logp_ref, advanta
         d_ptr, ldd = dlogits.data_ptr(), dlogits.stride(0)
     else:
         out.dlogits = None
-        d_ptr, ldd = None, 0
-    p = _lib.DppoParams(float(band[0]), float(band[1]), float(clip_eps[0]), float(clip_eps[1]),
-                        RD_MODES[rd_mode], SCALE_MODES[scale_mode], float(loss_scale),
-                        REF_MODES[ref_mode], float(alpha))
-    st = _lib.lib().decoupled_ppo_loss_fwd_bwd(
-        ptr, _dtype_code(logits), T, V, ld, ids, mu, ref, adv, msk, tsc, C.byref(p),
+        d_ptr, ldd = 0, 0
+    # None pointers are 0; the order is dppo_loss_call's
+    call = _lib.pack_loss_call(
+        ptr, _dtype_code(logits), T, V, ld, ids, mu, ref or 0, adv, msk or 0, tsc or 0,
         out.logp.data_ptr(), out.loss_tok.data_ptr(), out.loss.data_ptr(),
-        out.flags.data_ptr() if out.flags is not None else None, d_ptr, ldd,
-        out.stats.data_ptr(), _stream(dev))
+        out.flags.data_ptr() if out.flags is not None else 0, d_ptr, ldd, out.stats.data_ptr(),
+        _stream(dev), float(band[0]), float(band[1]), float(clip_eps[0]), float(clip_eps[1]),
+        RD_MODES[rd_mode], SCALE_MODES[scale_mode], float(loss_scale), REF_MODES[ref_mode], float(alpha))
+    st = _lib.lib().decoupled_ppo_loss_call(call)
     _lib.check(st, "decoupled_ppo_loss_fwd_bwd")
     return out
 
@@ -619,6 +622,7 @@ class DecoupledPPOLoss(torch.autograd.Function):
         res = decoupled_ppo_loss_fwd_bwd(logits, token_ids, logp_mu_old, logp_ref, advantages,
                                          loss_mask, token_scale, **(kwargs or {}))
         ctx.save_for_backward(res.dlogits)
+        ctx.set_materialize_grads(False)     # no zero fills for logp and stats
         ctx.mark_non_differentiable(res.logp, res.stats)
         # Flags and per-token losses of this call alone; buffers the caller owns (out=) may
         # hold a later call's by the time of the backward.
@@ -630,6 +634,8 @@ class DecoupledPPOLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_loss, g_lp, g_stats):
         (d,) = ctx.saved_tensors
+        if g_loss is None:
+            g_loss = torch.zeros((), dtype=torch.float32, device=d.device)
         if d.dim() == 2 and d.dtype in (torch.bfloat16, torch.float32) and _scalable(d, g_loss, d.dtype):
             T, V = d.shape
             flags, loss_tok = ctx.rows if ctx.rows is not None else (None, None)
@@ -667,6 +673,7 @@ class FusedLMHeadLoss(torch.autograd.Function):
                                          logp_mu_old, logp_ref, advantages, loss_mask,
                                          token_scale, want_grads=True, **(kwargs or {}))
         ctx.save_for_backward(res.dhidden, res.dweight)
+        ctx.set_materialize_grads(False)     # no zero fills for logp and stats
         ctx.dtypes = (hidden.dtype, weight.dtype)
         ctx.mark_non_differentiable(res.logp, res.stats)
         return res.loss[0], res.logp, res.stats
@@ -674,6 +681,8 @@ class FusedLMHeadLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_loss, g_lp, g_stats):
         dh, dw = ctx.saved_tensors
+        if g_loss is None:
+            g_loss = torch.zeros((), dtype=torch.float32, device=dh.device)
         th, tw = ctx.dtypes
         gh = FusedLMHeadLoss._scaled(dh, g_loss, th) if ctx.needs_input_grad[0] else None
         gw = FusedLMHeadLoss._scaled(dw, g_loss, tw) if ctx.needs_input_grad[1] else None

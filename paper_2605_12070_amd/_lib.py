@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 import threading
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdppo.so")
@@ -41,10 +42,23 @@ class DppoEwmaState(C.Structure):
                 ("ca", C.c_float), ("cb", C.c_float), ("reserved", C.c_int32)]
 
 
+# dppo_loss_call: 19 pointers and 64-bit integers, dppo_params, padding to 8 bytes.
+LOSS_CALL = struct.Struct("=19q4f2ifif4x")
+
+
+def pack_loss_call(*fields) -> bytes:
+    """A dppo_loss_call (fields in order, None for a NULL pointer already 0)."""
+    try:
+        return LOSS_CALL.pack(*fields)
+    except OverflowError:        # a finite float past float32's range becomes infinite, as in C
+        return LOSS_CALL.pack(*(C.c_float(f).value if isinstance(f, float) else f for f in fields))
+
+
 SIGNATURES = {
     "logprob_fwd": (I32, [VP, I32, I64, I64, I64, VP, VP, VP, VP]),
     "decoupled_ppo_loss_fwd_bwd": (I32, [VP, I32, I64, I64, I64, VP, VP, VP, VP, VP, VP,
                                          C.POINTER(DppoParams), VP, VP, VP, VP, VP, I64, VP, VP]),
+    "decoupled_ppo_loss_call": (I32, [C.c_char_p]),
     "ewma_proxy_update": (I32, [VP, VP, I32, I64, F32, C.POINTER(C.c_double), I32, I32, VP]),
     "ewma_proxy_step": (I32, [VP, VP, I32, I64, F32, F64, I32, I32, VP, VP, VP]),
     "vocab_shard_stats": (I32, [VP, I32, I64, I64, I64, I64, I64, VP, VP, VP, VP, VP]),

@@ -516,6 +516,16 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
   return DPPO_OK;
 }
 
+dppo_status decoupled_ppo_loss_call(const dppo_loss_call* c) {
+  if (!c) return fail(DPPO_ERR_INVALID_ARG, "call pointer is NULL");
+  if (c->dtype != DPPO_F32 && c->dtype != DPPO_BF16)
+    return fail(DPPO_ERR_INVALID_ARG, "unknown dtype %lld", (long long)c->dtype);
+  return decoupled_ppo_loss_fwd_bwd(
+      c->logits, (int32_t)c->dtype, c->T, c->V, c->ld, c->token_ids, c->logp_mu_old, c->logp_ref,
+      c->advantages, c->loss_mask, c->token_scale, &c->params, c->logp_out, c->loss_tok_out,
+      c->loss_out, c->flags_out, c->dlogits, c->ld_dlogits, c->stats_out, c->stream);
+}
+
 int64_t fused_lm_head_workspace_bytes(int64_t T, int64_t d, int64_t V, int64_t vocab_chunk) {
   if (T < 0 || d < 8 || V < 1 || T >= ((int64_t)1 << 31) || V > ((int64_t)1 << 21)) return -1;
   return lmh_layout(T, V, vocab_chunk).total;

@@ -502,3 +502,27 @@ def test_noalloc_rejects_sizes_beyond_its_scratch():
     assert L.fused_lm_head_loss_fwd_bwd_noalloc(*args(16, (1 << 21) + 1)) == _lib.DPPO_ERR_INVALID_ARG
     assert used.value == -7
 
+
+
+def test_packed_loss_call_is_the_header_struct():
+    """The packed call's bytes read back as the header's struct, floats past float32's range
+    become infinite as a C conversion makes them, and the checks are those of the long call."""
+    class Call(C.Structure):
+        _fields_ = [(f"f{i}", C.c_int64) for i in range(19)] + [("params", _lib.DppoParams)]
+
+    assert C.sizeof(Call) == _lib.LOSS_CALL.size
+    b = _lib.pack_loss_call(*range(100, 119), 0.5, 1e39, 0.25, 0.125, 3, 1, 2.0, 2, 0.75)
+    c = Call.from_buffer_copy(b)
+    assert [getattr(c, f"f{i}") for i in range(19)] == list(range(100, 119))
+    p = c.params
+    assert (p.band_lo, p.band_hi, p.clip_eps_lo, p.clip_eps_hi) == (0.5, float("inf"), 0.25, 0.125)
+    assert (p.rd_mode, p.scale_mode, p.loss_scale, p.ref_mode, p.alpha) == (3, 1, 2.0, 2, 0.75)
+    L = _lib.lib()
+    good = [FAKE, 1, 4, 8, 8, FAKE, FAKE, FAKE, FAKE, 0, 0, FAKE, FAKE, FAKE, 0, 0, 0, FAKE, 0]
+    prm = [0.5, 2.0, 0.2, 0.2, 3, 1, 1.0, 0, 0.5]
+    for at, bad in ((1, 7), (1, (1 << 32) + 1), (2, -1), (4, 7), (5, 0), (17, 0)):
+        f = list(good)
+        f[at] = bad
+        assert L.decoupled_ppo_loss_call(_lib.pack_loss_call(*f, *prm)) == 1, at
+    assert L.decoupled_ppo_loss_call(_lib.pack_loss_call(*good, *prm[:3], -0.1, *prm[4:])) == 1
+    assert L.decoupled_ppo_loss_call(None) == 1
