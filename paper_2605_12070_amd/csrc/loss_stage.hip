@@ -218,8 +218,10 @@ __device__ __forceinline__ void finish_row(const RowArgs& a, int64_t row, float 
 // Rows may start and end anywhere: a row is read as the aligned chunks that cover it, entries of
 // the neighbouring rows count as -inf and are never written (dlogits has the logits' phase). Whole calls, with the counter atomics gone as well (forward and backward, as
 // workgroups per row against this): bf16 T = 4573, V = 1521 70 -> 23 us, T = 5065, V = 6373
-// 80 -> 39 us, T = 16384, V = 8192 134 -> 117 us; fp32 T = 16384, V = 2000 67 -> 63 us, V = 4000
-// the same; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, T = 13324, V = 1616 fp32 33 -> 16 us.
+// 80 -> 39 us, T = 16384, V = 8192 134 -> 116 us, T = 16000, V = 9000 166 -> 125 us, V = 12288 170 ->
+// 161 us (at 16384 entries the workgroup kernels are as fast); fp32 T = 16384, V = 2000 67 -> 61 us,
+// V = 4000 the same, V = 5000 145 -> 136 us; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, V = 9001
+// 112 -> 48 us, V = 12288 126 -> 64 us, fp32 V = 6000 93 -> 58 us.
 // ---------------------------------------------------------------------------------------
 constexpr int kWaveNT = 256;
 
@@ -1685,8 +1687,8 @@ struct ResCfg {
   int nt, nc;
 };
 // Resident shapes, by capacity in 16-byte chunks (NT * NC).
-constexpr ResCfg kResident[] = {{256, 1},  {256, 2},   {256, 4},   {512, 4},   {512, 6},
-                                {512, 8},  {1024, 6}, {1024, 8}, {1024, 12}, {1024, 19}};
+constexpr ResCfg kResident[] = {{256, 1}, {256, 2},  {256, 4},  {256, 6},   {512, 4},  {512, 6},
+                                {512, 8}, {1024, 6}, {1024, 8}, {1024, 12}, {1024, 19}};
 constexpr int kNumResident = sizeof(kResident) / sizeof(kResident[0]);
 // Per-shape launch choices, each from same-box A/B timings at T = 16384 (MI355X):
 //  * bf16 backward with two row buffers: 5-10 % faster for 512 x 4 .. 1024 x 8; within
@@ -1694,10 +1696,10 @@ constexpr int kNumResident = sizeof(kResident) / sizeof(kResident[0]);
 //  * fp32 persistent (a loop over rows, counters flushed once per workgroup) rather than one
 //    workgroup per row: 2-6x faster up to 512 x 8 and 6 % at 1024 x 19, 0-7 % slower for
 //    1024 x 6 .. 1024 x 12.
-constexpr bool kResidentDB[kNumResident] = {false, false, false, true, true,
+constexpr bool kResidentDB[kNumResident] = {false, false, false, false, true, true,
                                             true,  true,  true,  false, false};
-constexpr bool kF32Persistent[kNumResident] = {true,  true,  true,  true,  true,
-                                               true,  false, false, false, true};
+constexpr bool kF32Persistent[kNumResident] = {true, true,  true,  true,  true, true,
+                                               true, false, false, false, true};
 // Persistent grids launch kFill* of every 32 resident workgroup slots. A gradient kernel
 // moves fewer bytes per second with every CU streaming than with a few CUs of each XCD
 // idle; the read-only forward kernels mostly want every slot. Same-box A/B at T = 16384 over
@@ -1709,11 +1711,11 @@ constexpr bool kF32Persistent[kNumResident] = {true,  true,  true,  true,  true,
 // (T = 4096, count mode): 31 gives a 1.4-1.7 % shorter step than 29 (27: 1.6 % longer, 30:
 // 0.6 % shorter, 32: 0.3 % shorter; same-process runs), the same time at
 // T = 16384, 0.3-0.5 % less at T = 8192 and 1-2 % more at T = 2048.
-// Shapes:                                   256x1 256x2 256x4 512x4 512x6 512x8 1Kx6 1Kx8 1Kx12 1Kx19
-constexpr int kFillBf16Bwd[kNumResident] = {32,   32,   32,   32,   29,   31,   27,  27,  29,   27};
-constexpr int kFillBf16Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   32,  32,  30,   30};
-constexpr int kFillF32Bwd[kNumResident] = {32,   32,   32,   30,   30,   30,   27,  27,  27,   25};
-constexpr int kFillF32Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   27,  27,  27,   32};
+// Shapes:                                   256x1 256x2 256x4 256x6 512x4 512x6 512x8 1Kx6 1Kx8 1Kx12 1Kx19
+constexpr int kFillBf16Bwd[kNumResident] = {32,   32,   32,   32,   32,   29,   31,   27,  27,  29,   27};
+constexpr int kFillBf16Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   32,   32,  32,  30,   30};
+constexpr int kFillF32Bwd[kNumResident] = {32,   32,   32,   32,   30,   30,   30,   27,  27,  27,   25};
+constexpr int kFillF32Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   32,   27,  27,  27,   32};
 // Measured: bf16 backward and forward; the 256-thread kernels (a row per wave) 32 against 27
 // (2-5 % slower) and 24 (2 % either way); fp32 backward 512 x 4, 512 x 8 and 1024 x 19; fp32
 // forward 512 x 4 and 1024 x 19. fp32 backward 1024 x 6 .. 12 run one workgroup per row (kF32Persistent), so their fill is unused.
@@ -1724,21 +1726,22 @@ constexpr int kFillBf16Prefix = 31;
 // sweeps of 0 to 6: the flagship is fastest at 4 (0.5 % faster than 2), 512 x 4 backward and
 // 512 x 8 forward at 0 (4 %), the small_vocab shape (512 x 8 backward, T = 4096) at 1 (1 %);
 // 1024 x 8 and 1024 x 12 backward are flat from 1 to 4.
-// Shapes:                                   256x1 256x2 256x4 512x4 512x6 512x8 1Kx6 1Kx8 1Kx12 1Kx19
-constexpr int kStagBf16Bwd[kNumResident] = {0,    0,    0,    0,    1,    1,    2,   2,   2,    4};
-constexpr int kStagBf16Fwd[kNumResident] = {0,    0,    0,    0,    0,    0,    1,   1,   2,    2};
+// Shapes:                                   256x1 256x2 256x4 256x6 512x4 512x6 512x8 1Kx6 1Kx8 1Kx12 1Kx19
+constexpr int kStagBf16Bwd[kNumResident] = {0,    0,    0,    0,    0,    1,    1,    2,   2,   2,    4};
+constexpr int kStagBf16Fwd[kNumResident] = {0,    0,    0,    0,    0,    0,    0,    1,   1,   2,    2};
 
 const void* pick_bf16_fwd(int i) {
   switch (i) {
     case 0: return (const void*)rows_bf16_fwd<256, 1>;
     case 1: return (const void*)rows_bf16_fwd<256, 2>;
     case 2: return (const void*)rows_bf16_fwd<256, 4>;
-    case 3: return (const void*)rows_bf16_fwd<512, 4>;
-    case 4: return (const void*)rows_bf16_fwd<512, 6>;
-    case 5: return (const void*)rows_bf16_fwd<512, 8>;
-    case 6: return (const void*)rows_bf16_fwd<1024, 6>;
-    case 7: return (const void*)rows_bf16_fwd<1024, 8>;
-    case 8: return (const void*)rows_bf16_fwd<1024, 12>;
+    case 3: return (const void*)rows_bf16_fwd<256, 6>;
+    case 4: return (const void*)rows_bf16_fwd<512, 4>;
+    case 5: return (const void*)rows_bf16_fwd<512, 6>;
+    case 6: return (const void*)rows_bf16_fwd<512, 8>;
+    case 7: return (const void*)rows_bf16_fwd<1024, 6>;
+    case 8: return (const void*)rows_bf16_fwd<1024, 8>;
+    case 9: return (const void*)rows_bf16_fwd<1024, 12>;
     default: return (const void*)rows_bf16_fwd<1024, 19>;
   }
 }
@@ -1747,22 +1750,23 @@ const void* pick_bf16_fwd_phase(int i) {
     case 0: return (const void*)rows_bf16_fwd_phase<256, 1>;
     case 1: return (const void*)rows_bf16_fwd_phase<256, 2>;
     case 2: return (const void*)rows_bf16_fwd_phase<256, 4>;
-    case 3: return (const void*)rows_bf16_fwd_phase<512, 4>;
-    case 4: return (const void*)rows_bf16_fwd_phase<512, 6>;
-    case 5: return (const void*)rows_bf16_fwd_phase<512, 8>;
-    case 6: return (const void*)rows_bf16_fwd_phase<1024, 6>;
-    case 7: return (const void*)rows_bf16_fwd_phase<1024, 8>;
-    case 8: return (const void*)rows_bf16_fwd_phase<1024, 12>;
+    case 3: return (const void*)rows_bf16_fwd_phase<256, 6>;
+    case 4: return (const void*)rows_bf16_fwd_phase<512, 4>;
+    case 5: return (const void*)rows_bf16_fwd_phase<512, 6>;
+    case 6: return (const void*)rows_bf16_fwd_phase<512, 8>;
+    case 7: return (const void*)rows_bf16_fwd_phase<1024, 6>;
+    case 8: return (const void*)rows_bf16_fwd_phase<1024, 8>;
+    case 9: return (const void*)rows_bf16_fwd_phase<1024, 12>;
     default: return (const void*)rows_bf16_fwd_phase<1024, 19>;
   }
 }
 const void* pick_bf16_phase_db(int i) {
   switch (i) {
-    case 3: return (const void*)rows_bf16_phase_db<512, 4>;
-    case 4: return (const void*)rows_bf16_phase_db<512, 6>;
-    case 5: return (const void*)rows_bf16_phase_db<512, 8>;
-    case 6: return (const void*)rows_bf16_phase_db<1024, 6>;
-    case 7: return (const void*)rows_bf16_phase_db<1024, 8>;
+    case 4: return (const void*)rows_bf16_phase_db<512, 4>;
+    case 5: return (const void*)rows_bf16_phase_db<512, 6>;
+    case 6: return (const void*)rows_bf16_phase_db<512, 8>;
+    case 7: return (const void*)rows_bf16_phase_db<1024, 6>;
+    case 8: return (const void*)rows_bf16_phase_db<1024, 8>;
     default: return nullptr;
   }
 }
@@ -1772,23 +1776,24 @@ const void* pick_bf16_phase(int i) {
     case 0: return (const void*)rows_bf16_phase<256, 1, BWD>;
     case 1: return (const void*)rows_bf16_phase<256, 2, BWD>;
     case 2: return (const void*)rows_bf16_phase<256, 4, BWD>;
-    case 3: return (const void*)rows_bf16_phase<512, 4, BWD>;
-    case 4: return (const void*)rows_bf16_phase<512, 6, BWD>;
-    case 5: return (const void*)rows_bf16_phase<512, 8, BWD>;
-    case 6: return (const void*)rows_bf16_phase<1024, 6, BWD>;
-    case 7: return (const void*)rows_bf16_phase<1024, 8, BWD>;
-    case 8: return (const void*)rows_bf16_phase<1024, 12, BWD>;
+    case 3: return (const void*)rows_bf16_phase<256, 6, BWD>;
+    case 4: return (const void*)rows_bf16_phase<512, 4, BWD>;
+    case 5: return (const void*)rows_bf16_phase<512, 6, BWD>;
+    case 6: return (const void*)rows_bf16_phase<512, 8, BWD>;
+    case 7: return (const void*)rows_bf16_phase<1024, 6, BWD>;
+    case 8: return (const void*)rows_bf16_phase<1024, 8, BWD>;
+    case 9: return (const void*)rows_bf16_phase<1024, 12, BWD>;
     default: return (const void*)rows_bf16_phase<1024, 19, BWD>;
   }
 }
 // Two-buffer backward kernels, for the shapes kResidentDB selects.
 const void* pick_bf16_db(int i) {
   switch (i) {
-    case 3: return (const void*)rows_bf16_resident_db<512, 4>;
-    case 4: return (const void*)rows_bf16_resident_db<512, 6>;
-    case 5: return (const void*)rows_bf16_resident_db<512, 8>;
-    case 6: return (const void*)rows_bf16_resident_db<1024, 6>;
-    case 7: return (const void*)rows_bf16_resident_db<1024, 8>;
+    case 4: return (const void*)rows_bf16_resident_db<512, 4>;
+    case 5: return (const void*)rows_bf16_resident_db<512, 6>;
+    case 6: return (const void*)rows_bf16_resident_db<512, 8>;
+    case 7: return (const void*)rows_bf16_resident_db<1024, 6>;
+    case 8: return (const void*)rows_bf16_resident_db<1024, 8>;
     default: return nullptr;
   }
 }
@@ -1798,12 +1803,13 @@ const void* pick_bf16(int i) {
     case 0: return (const void*)rows_bf16_resident<256, 1, BWD>;
     case 1: return (const void*)rows_bf16_resident<256, 2, BWD>;
     case 2: return (const void*)rows_bf16_resident<256, 4, BWD>;
-    case 3: return (const void*)rows_bf16_resident<512, 4, BWD>;
-    case 4: return (const void*)rows_bf16_resident<512, 6, BWD>;
-    case 5: return (const void*)rows_bf16_resident<512, 8, BWD>;
-    case 6: return (const void*)rows_bf16_resident<1024, 6, BWD>;
-    case 7: return (const void*)rows_bf16_resident<1024, 8, BWD>;
-    case 8: return (const void*)rows_bf16_resident<1024, 12, BWD>;
+    case 3: return (const void*)rows_bf16_resident<256, 6, BWD>;
+    case 4: return (const void*)rows_bf16_resident<512, 4, BWD>;
+    case 5: return (const void*)rows_bf16_resident<512, 6, BWD>;
+    case 6: return (const void*)rows_bf16_resident<512, 8, BWD>;
+    case 7: return (const void*)rows_bf16_resident<1024, 6, BWD>;
+    case 8: return (const void*)rows_bf16_resident<1024, 8, BWD>;
+    case 9: return (const void*)rows_bf16_resident<1024, 12, BWD>;
     default: return (const void*)rows_bf16_resident<1024, 19, BWD>;
   }
 }
@@ -1819,12 +1825,13 @@ const void* pick_f32(int i) {
     case 0: return (const void*)rows_f32_resident<256, 1, BWD>;
     case 1: return (const void*)rows_f32_resident<256, 2, BWD>;
     case 2: return (const void*)rows_f32_resident<256, 4, BWD>;
-    case 3: return (const void*)rows_f32_resident<512, 4, BWD>;
-    case 4: return (const void*)rows_f32_resident<512, 6, BWD>;
-    case 5: return (const void*)rows_f32_resident<512, 8, BWD>;
-    case 6: return (const void*)rows_f32_resident<1024, 6, BWD>;
-    case 7: return (const void*)rows_f32_resident<1024, 8, BWD>;
-    case 8: return (const void*)rows_f32_resident<1024, 12, BWD>;
+    case 3: return (const void*)rows_f32_resident<256, 6, BWD>;
+    case 4: return (const void*)rows_f32_resident<512, 4, BWD>;
+    case 5: return (const void*)rows_f32_resident<512, 6, BWD>;
+    case 6: return (const void*)rows_f32_resident<512, 8, BWD>;
+    case 7: return (const void*)rows_f32_resident<1024, 6, BWD>;
+    case 8: return (const void*)rows_f32_resident<1024, 8, BWD>;
+    case 9: return (const void*)rows_f32_resident<1024, 12, BWD>;
     default: return (const void*)rows_f32_resident<1024, 19, BWD>;
   }
 }

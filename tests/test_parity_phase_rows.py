@@ -320,10 +320,11 @@ SHORT_CASES = [  # dtype, T, V, extra columns per row, element offset of row 0
     ("bf16", 41, 2, 0, 5), ("bf16", 42, 8, 0, 0), ("bf16", 43, 511, 0, 1), ("bf16", 41, 512, 8, 0),
     ("bf16", 90, 513, 1, 7), ("bf16", 37, 2041, 0, 7), ("bf16", 64, 2048, 0, 0), ("bf16", 33, 2049, 0, 0),
     ("bf16", 30, 4089, 7, 7), ("bf16", 31, 4096, 0, 0), ("bf16", 30, 4097, 0, 3), ("bf16", 29, 8185, 0, 7),
+    ("bf16", 30, 8193, 0, 0), ("bf16", 29, 12281, 0, 7), ("bf16", 30, 12288, 0, 0),
     ("bf16", 5000, 600, 0, 3),
     ("f32", 43, 255, 0, 1), ("f32", 41, 256, 0, 0), ("f32", 42, 1021, 0, 3), ("f32", 41, 1024, 4, 0),
     ("f32", 33, 1025, 0, 0), ("f32", 30, 2045, 0, 3), ("f32", 31, 2048, 0, 0), ("f32", 29, 4093, 0, 3),
-    ("f32", 30, 4096, 0, 0), ("f32", 5000, 300, 0, 1),
+    ("f32", 30, 4096, 0, 0), ("f32", 29, 6141, 0, 3), ("f32", 30, 6144, 0, 0), ("f32", 5000, 300, 0, 1),
 ]
 
 
