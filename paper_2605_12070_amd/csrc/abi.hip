@@ -471,10 +471,9 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
     L = dppo::select_row_kernel(dtype, V, aligned, dlogits != nullptr, g_path_policy, phase_ok);
     cover_short_rows(L, T * V * es, true);
   }
-  // Count mode: a persistent fp32 resident row kernel on a batch short enough for every
-  // workgroup to read the mask counts the valid tokens itself and loss_sum takes the
-  // counters from the flags, so prep_stats does not run (one launch fewer per call: the
-  // tiny configuration's step 40.6 -> 36.6 us).
+  // Count mode: a persistent row kernel that can (RowLaunch::counts), on a batch short enough for
+  // every workgroup to read the mask, counts the valid tokens itself, so prep_stats does not
+  // run (one launch fewer per call: the tiny configuration's step 40.6 -> 36.6 us).
   // A call that writes flags takes the counters from them in loss_sum: the row kernels' counter
   // atomics serialise (one add per workgroup and counter, five addresses): T = 4573, V = 1521
   // bf16 63 us with 1512 workgroups' atomics. The single-buffer bf16 gradient kernels of long

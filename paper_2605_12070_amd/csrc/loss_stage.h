@@ -47,7 +47,7 @@ struct RowArgs {
   float alpha;          // behaviour-policy weight of an interpolated reference
   int32_t stagger;      // persistent bf16 kernels: start delay per XCD-local workgroup index,
                         // in s_sleep(6) units (set by the launcher from RowLaunch)
-  int32_t count_mode;   // 1 (persistent fp32 resident loss calls that write flags): no
+  int32_t count_mode;   // 1 (persistent loss calls that write flags, RowLaunch::counts): no
                         // prep_stats; each workgroup counts the valid tokens itself for the
                         // token-mean scale (workgroup 0 stores the count)
   int32_t flag_counts;  // 1 (calls that write flags): no counter atomics; loss_sum derives the
