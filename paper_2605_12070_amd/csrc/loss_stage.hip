@@ -15,6 +15,7 @@
 #include "dppo.h"
 #include "dppo_device.h"
 #include "loss_stage.h"
+#include "row_split.h"
 #include "token_math.h"
 
 namespace dppo {
@@ -113,24 +114,6 @@ __device__ float call_scale(const RowArgs& a) {
   return a.loss_scale / (float)(n > 1 ? n : 1);
 }
 
-// A row of V entries cut into its whole aligned 16-byte chunks and the entries before and after
-// them (fewer than a chunk at each end): nfull chunks from entry `lead` on, nedge single
-// entries, the i-th of them entry<E>(i).
-struct RowSplit {
-  int lead, nfull, nedge;
-  template <int E>
-  __device__ __forceinline__ int entry(int i) const { return i < lead ? i : nfull * E + i; }
-};
-template <typename Tin>
-__device__ __forceinline__ RowSplit split_row(const Tin* row, int V) {
-  constexpr int E = 16 / (int)sizeof(Tin);
-  RowSplit sp;
-  sp.lead = min(V, (int)((0u - (uint32_t)(uintptr_t)row) & 15u) / (int)sizeof(Tin));
-  sp.nfull = (V - sp.lead) / E;
-  sp.nedge = V - sp.nfull * E;
-  return sp;
-}
-
 // Zeros for a gradient row of V entries at any alignment: 16-byte stores over the whole chunks
 // inside it, single entries before and after them.
 template <typename Tin, int NT>
@@ -215,13 +198,16 @@ __device__ __forceinline__ void finish_row(const RowArgs& a, int64_t row, float 
 // those of resident_rows for bf16 (an integer log2 shift per chunk, exponentials kept as fp16
 // pairs); an fp32 row is shifted by its maximum, as the general kernels' merged result is, and
 // keeps fp32 exponentials.
-// Rows may start and end anywhere: a row is read as the aligned chunks that cover it, entries of
-// the neighbouring rows count as -inf and are never written (dlogits has the logits' phase). Whole calls, with the counter atomics gone as well (forward and backward, as
-// workgroups per row against this): bf16 T = 4573, V = 1521 70 -> 23 us, T = 5065, V = 6373
-// 80 -> 39 us, T = 16384, V = 8192 134 -> 116 us, T = 16000, V = 9000 166 -> 125 us, V = 12288 170 ->
-// 161 us (at 16384 entries the workgroup kernels are as fast); fp32 T = 16384, V = 2000 67 -> 61 us,
-// V = 4000 the same, V = 5000 145 -> 136 us; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, V = 9001
-// 112 -> 48 us, V = 12288 126 -> 64 us, fp32 V = 6000 93 -> 58 us.
+// Rows may start and end anywhere (dlogits has the logits' phase). A bf16 row is read as the
+// aligned chunks that cover it; entries of the neighbouring rows count as -inf and are never
+// written. An fp32 row is its whole aligned chunks and up to three entries at each end, one per
+// lane: nothing outside it is read (WaveSpan).
+// Whole calls, with the counter atomics gone as well (forward and backward, as workgroups per row
+// against this): bf16 T = 4573, V = 1521 70 -> 23 us, T = 5065, V = 6373 80 -> 39 us, T = 16384,
+// V = 8192 134 -> 116 us, T = 16000, V = 9000 166 -> 125 us, V = 12288 170 -> 161 us (at 16384
+// entries the workgroup kernels are as fast); fp32 T = 16384, V = 2000 67 -> 61 us, V = 4000 the
+// same, V = 5000 145 -> 136 us; log-probs T = 16000, V = 1601 bf16 40 -> 15 us, V = 9001 112 -> 48 us,
+// V = 12288 126 -> 64 us, fp32 V = 6000 93 -> 58 us.
 // ---------------------------------------------------------------------------------------
 constexpr int kWaveNT = 256;
 
@@ -269,18 +255,23 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
       continue;
     }
     // entry k of this lane's chunk c lies inside the row iff lo(c) <= k < hi(c)
-    const int ph = (int)(((uintptr_t)zrow / sizeof(Tin)) & (E - 1));
-    const int end = ph + V;                  // in entries from the first chunk's start
-    const int bytes = ((end + E - 1) / E) * 16;
-    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow - ph, bytes);
+    const WaveSpan span = wave_span(zrow, V);
+    const __amdgpu_buffer_rsrc_t rz = row_rsrc(zrow + span.first, span.bytes);
     const int voff = lane * 16;
-    auto lo = [&](int c) { return ph - E * (c * 64 + lane); };
-    auto hi = [&](int c) { return end - E * (c * 64 + lane); };
-    auto any = [&](int c) { return E * c * 64 < end; };                    // uniform
-    auto whole = [&](int c) { return (c > 0 || ph == 0) && E * (c + 1) * 64 <= end; };
+    auto lo = [&](int c) { return span.lo - E * (c * 64 + lane); };
+    auto hi = [&](int c) { return span.hi - E * (c * 64 + lane); };
+    auto any = [&](int c) { return E * c * 64 < span.hi; };                // uniform
+    auto whole = [&](int c) { return (c > 0 || span.lo == 0) && E * (c + 1) * 64 <= span.hi; };
     uint32_t r[M][4];
 #pragma unroll
     for (int c = 0; c < M; ++c) load16<kAuxLast>(r[c], rz, voff, c * 1024);
+    // fp32: this lane's entry before or after the whole chunks, if it has one
+    const bool edge = !BF && lane < span.nedge;
+    const int ei = RowSplit{span.first, span.bytes / 16, span.nedge}.entry<E>(lane);
+    float xe = -INFINITY;
+    if constexpr (!BF)
+      xe = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_rsrc(zrow, V * 4),
+                                                                edge ? ei * 4 : 0x7fffff00, 0, kAuxLast));
     // z[y] (a bad id of a log-prob call reads the row's first entry, unused)
     const uintptr_t at = (uintptr_t)(zrow + (good ? y : 0));
     const uint32_t zword = uload((const uint32_t*)(at & ~(uintptr_t)3));
@@ -328,7 +319,8 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
         asm volatile("" : "+v"(N), "+v"(S));
       }
     } else {
-      float m = -INFINITY;
+      if (!edge) xe = -INFINITY;
+      float m = xe;
 #pragma unroll
       for (int c = 0; c < M; ++c) {
         if (!any(c)) continue;
@@ -342,7 +334,8 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
       m = wave_max(m);
       N = (m == -INFINITY) ? -INFINITY : m * kLog2e;
       const float sh = (m == -INFINITY) ? 0.0f : N;
-      float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+      xe = exp2_hw(__builtin_fmaf(xe, kLog2e, -sh));
+      float s0 = xe, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll
       for (int c = 0; c < M; ++c) {
         if (!any(c)) continue;
@@ -374,7 +367,7 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
     }
     if (!BWD || !a.dlogits) continue;
     Tin* drow = (Tin*)a.dlogits + row * a.ldd;
-    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow - ph, bytes);
+    const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow + span.first, span.bytes);
     const float ff = row_factor(o.w, N, lse2);      // fp32
 #pragma unroll
     for (int c = 0; c < M; ++c) {
@@ -391,26 +384,22 @@ __device__ __forceinline__ void wave_rows(const RowArgsOf<BWD>& a) {
       }
       if (whole(c) || (lo(c) <= 0 && hi(c) >= E)) {
         buf_store16_nt(v, rd, voff, c * 1024);
-      } else {
+      } else if constexpr (BF) {            // an fp32 chunk is the row's as a whole or not at all
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          if (k >= lo(c) && k < hi(c)) {
-            if constexpr (BF)
-              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[k >> 1] >> (16 * (k & 1))), rd, voff + 2 * k,
-                                                    c * 1024, kAuxNT);
-            else
-              __builtin_amdgcn_raw_buffer_store_b32(v[k], rd, voff + 4 * k, c * 1024, kAuxNT);
-          }
-        }
+        for (int k = 0; k < E; ++k)
+          if (k >= lo(c) && k < hi(c))
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[k >> 1] >> (16 * (k & 1))), rd, voff + 2 * k,
+                                                  c * 1024, kAuxNT);
       }
     }
     // the sampled entry, by the lane whose chunk holds it, behind that chunk's store (two
     // stores of one lane to one address, through the same path, land in program order)
-    const int ey = (int)y + ph;
-    if (lane == ((ey / E) & 63)) {
+    const int ey = (int)y - span.first;
+    if (ey >= span.lo && ey < span.hi && lane == ((ey / E) & 63)) {
       if constexpr (BF) __builtin_amdgcn_raw_buffer_store_b16(to_bf16(o.dy), rd, ey * 2, 0, kAuxNT);
       else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.dy), rd, ey * 4, 0, kAuxNT);
     }
+    if (edge) drow[ei] = (Tin)(ei == y ? o.dy : xe * ff);
   }
   if (a.flag_counts || !loss_mode) return;   // uniform over the grid
   if (lane == 0) {
