@@ -1385,17 +1385,22 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
 // end anywhere (RowSplit).
 // ---------------------------------------------------------------------------------------
 // PH: rows that start anywhere. (The fp32 kernel takes them without a variant of its own; here
-// the run-time offset cost the aligned rows 2 %.)
+// the run-time offset cost the aligned rows 2 %.) Their resident chunks stay logits, and the whole
+// gradient is formed from them in fp32, as the streaming kernel forms it: fp16 exponentials would
+// round once more and lose the entries below 2^-24 of their chunk's maximum. No shift table then,
+// so the next KS = 9 chunks of a thread wait in LDS. T = 2048: V = 155661 290 us (fp16
+// exponentials 287, streaming entry by entry 1113), V = 262143 504 us (485, 2043), V = 400001
+// 743 us (746, 3388).
 template <int NT, int NC, bool PH>
 __device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
   constexpr int P = NT * NC;              // resident chunks of a row
   constexpr int U = 4;                    // tail chunks per thread in flight
   // the first KS of each thread's tail chunks also wait in LDS between the passes (each
   // thread reads back only what it wrote), beside the shift table
-  constexpr int KS = kPrefixKeepBf16;
+  constexpr int KS = PH ? kPrefixKeepF32 : kPrefixKeepBf16;
   __shared__ float red[2 * (NT / 64) + 2];
   __shared__ Bcast bc;
-  __shared__ float nch[NC][NT];           // per-chunk shifts, [c][tid]: conflict-free
+  __shared__ float nch[PH ? 1 : NC][NT];  // per-chunk shifts, [c][tid]: conflict-free
   __shared__ u32x4 keep[KS * NT];
   StatCount sc;
   // the call's scale (token-mean: from the valid-token count, fixed while the kernel runs)
@@ -1461,7 +1466,8 @@ __device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
       const float ns = (x == -INFINITY) ? 0.0f : x * kLog2e;
       merge_ns(nt, st, (x == -INFINITY) ? -INFINITY : ns, exp2_hw(__builtin_fmaf(x, kLog2e, -ns)));
     }
-    // pass A, resident chunks: shift n_c = ceil(L max(chunk)), fp16 exponentials in place
+    // pass A, resident chunks: shift n_c = ceil(L max(chunk)), fp16 exponentials in place (PH:
+    // the logits stay)
     uint32_t r[NC][4];
 #pragma unroll
     for (int c = 0; c < NC; ++c) load16<kAuxLast>(r[c], rz, tid * 16, c * NT * 16);
@@ -1483,10 +1489,10 @@ __device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
       const float cs = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        r[c][k] = pack_f16(e[2 * k], e[2 * k + 1]);
+        if (!PH) r[c][k] = pack_f16(e[2 * k], e[2 * k + 1]);
         asm volatile("" : "+v"(r[c][k]));
       }
-      nch[c][tid] = nc;
+      if (!PH) nch[c][tid] = nc;
       merge_ns_int(N, S, nc, cs);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1501,21 +1507,29 @@ __device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
     const float l2 = bc.lse2;
     uint16_t* drow = (uint16_t*)a.dlogits + row * a.ldd;
     const __amdgpu_buffer_rsrc_t rd = row_rsrc(drow + sp.lead, nfull * 16);
-    // pass B, resident chunks: w 2^(n_c - lse2) e (the sampled entry: the thread that holds
-    // it); a NaN lse (non-finite row) makes every element NaN
+    // pass B, resident chunks: w 2^(n_c - lse2) e, or w 2^(z L - lse2) from the logits (the
+    // sampled entry: the thread that holds it); a NaN lse (non-finite row) makes every element NaN
     const int yb = (int)y - sp.lead;
     const int cy = yb >> 3;
     const int jy = yb & 7;
     const int my_slot = (yb >= 0 && cy < P && cy % NT == tid) ? cy / NT : -1;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const float ncv = nch[c][tid];
-      const float f = (l2 != l2) ? l2 : ((ncv == -INFINITY) ? 0.0f : w * exp2_hw(ncv - l2));
       float o[8];
+      if constexpr (PH) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        o[2 * k] = f16_lo_mul(r[c][k], f);
-        o[2 * k + 1] = f16_hi_mul(r[c][k], f);
+        for (int k = 0; k < 4; ++k) {
+          o[2 * k] = w * exp2_hw(__builtin_fmaf(bf16_lo(r[c][k]), kLog2e, -l2));
+          o[2 * k + 1] = w * exp2_hw(__builtin_fmaf(bf16_hi(r[c][k]), kLog2e, -l2));
+        }
+      } else {
+        const float ncv = nch[c][tid];
+        const float f = (l2 != l2) ? l2 : ((ncv == -INFINITY) ? 0.0f : w * exp2_hw(ncv - l2));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          o[2 * k] = f16_lo_mul(r[c][k], f);
+          o[2 * k + 1] = f16_hi_mul(r[c][k], f);
+        }
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) o[j] = (c == my_slot && j == jy) ? dy : o[j];

@@ -373,3 +373,28 @@ def test_counters_from_flags_and_from_atomics(dtype, T, V, grads):
         for r in (a, b, c):
             assert r.stats.tolist() == want
             assert torch.equal(r.loss.view(torch.int32), a.loss.view(torch.int32))
+
+
+@pytest.mark.parametrize("V,off", [(155661, 0), (155663, 5), (196625, 3), (262143, 1)])
+def test_long_unaligned_rows_keep_small_probabilities(V, off):
+    """bf16 rows that start anywhere and are longer than the resident kernels hold: their gradient
+    is formed in fp32 from the logits, so an entry far below its neighbours keeps its value and
+    every entry is rounded once, to bf16 (2^-8). Beside it the fp32 log-sum-exp and exponents of up
+    to 80 (2e-5). Each length has entries in the resident part and, past it, in the tail."""
+    T = 3
+    assert "rows_bf16_prefix_phase" in P.row_kernel_name(torch.bfloat16, V, V)
+    _say("long rows, small probabilities", V, off)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    buf = torch.zeros(off + T * V + 16, dtype=torch.bfloat16, device=DEV)
+    z = buf[off:off + T * V].view(T, V)
+    z.copy_(torch.randn(T, V, generator=g, device=DEV) - 30)
+    z[:, 3::13] += 40
+    ids = torch.tensor([3, 16, V - 1], device=DEV)
+    p = torch.softmax(z.double(), dim=1)
+    lp = p.gather(1, ids[:, None])[:, 0].log().float()
+    adv = torch.ones(T, device=DEV)
+    d = torch.empty_like(buf)[off:off + T * V].view(T, V)
+    P.decoupled_ppo_loss_fwd_bwd(z, ids, lp, lp, adv, dlogits=d, scale_mode="const")
+    torch.cuda.synchronize()
+    rel = ((d.double() - p) / p).scatter(1, ids[:, None], 0.0).abs().max()
+    assert rel <= 2.0 ** -8 + 2e-5, float(rel)
