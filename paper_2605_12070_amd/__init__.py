@@ -598,8 +598,11 @@ class EwmaProxyDevice:
 def _scalable(d: torch.Tensor, g: torch.Tensor, dtype: torch.dtype) -> bool:
     """True when the library's scale kernels can form d * g: plain tensors on the current
     device, outside a differentiated backward (create_graph) and outside vmap or tracing, whose
-    tensors have no data pointer."""
+    tensors have no data pointer. A lazily negated tensor (the imaginary part of a conjugate)
+    holds the other sign in memory."""
     if torch.is_grad_enabled() or type(d) is not torch.Tensor or type(g) is not torch.Tensor:
+        return False
+    if d.is_neg() or g.is_neg():
         return False
     if (d.dtype != dtype or g.dtype != torch.float32 or g.dim() != 0 or not d.is_cuda
             or d.device != g.device or d.device.index != torch.cuda.current_device()

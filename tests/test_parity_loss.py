@@ -775,3 +775,25 @@ def test_autograd_backward_differentiated_and_batched():
     us = torch.tensor([1.0, 3.0], device=DEV)
     (gb,) = torch.autograd.grad(loss, z, us, is_grads_batched=True)
     assert torch.equal(gb[1], 3.0 * d)
+
+
+def test_autograd_backward_of_a_lazily_negated_gradient():
+    """The upstream gradient as the imaginary part of a conjugate: torch hands on a view whose
+    memory holds the other sign. Both wrappers return the same gradient as for its value."""
+    wl = W.make_workload("tiny", device=DEV)
+    _say("autograd, negated view")
+    lp = torch.full((wl.T,), -7.0, device=DEV)
+    u = torch.complex(torch.tensor(1.0, device=DEV), torch.tensor(2.0, device=DEV)).conj().imag
+    assert u.is_neg() and u.item() == -2.0
+    z = wl.logits.clone().requires_grad_(True)
+    loss, _, _ = P.DecoupledPPOLoss.apply(z, wl.ids, lp, lp, wl.adv, None, None, None)
+    (a,) = torch.autograd.grad(loss, z, u, retain_graph=True)
+    (b,) = torch.autograd.grad(loss, z, u.clone())
+    assert a.abs().max() > 0 and torch.equal(a, b)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    h = torch.randn(wl.T, 64, generator=g, device=DEV).to(torch.bfloat16).requires_grad_(True)
+    w = torch.randn(wl.V, 64, generator=g, device=DEV).to(torch.bfloat16).requires_grad_(True)
+    loss, _, _ = P.FusedLMHeadLoss.apply(h, w, wl.ids, lp, lp, wl.adv, None, None, None)
+    a = torch.autograd.grad(loss, (h, w), u, retain_graph=True)
+    b = torch.autograd.grad(loss, (h, w), u.clone())
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
