@@ -111,9 +111,12 @@ hipError_t resident_slots(const dppo::RowLaunch& L, int64_t* slots) {
 // T = 16000 bf16 with gradients V = 8200, 40 % masked 108 / 100 us, V = 12000 166 / 158 us; log-probs
 // V = 9001 52 / 48 us; T = 5438, V = 3264 (35 MB) 28.7 / 31.0 us, T = 16384, V = 2048 (64 MB) 43.7 /
 // 40.9 us.
+// A loss call whose counters are not derived from its flags keeps the persistent grid at any size:
+// a workgroup ends in up to four atomics on the same addresses, which serialise. T = 262144,
+// V = 1024 bf16 without flags: 2387 us covering, 385 us persistent; with flags 371 us covering.
 constexpr int64_t kCoverBytes = (int64_t)64 << 20;
-void cover_short_rows(dppo::RowLaunch& L, int64_t bytes, bool loss) {
-  if (L.rows_per_group > 1 && (!loss || bytes >= kCoverBytes)) L.persistent = false;
+void cover_short_rows(dppo::RowLaunch& L, int64_t bytes, bool loss, bool flag_counts) {
+  if (L.rows_per_group > 1 && (!loss || (flag_counts && bytes >= kCoverBytes))) L.persistent = false;
 }
 
 dppo_status launch_rows(const dppo::RowLaunch& L, const dppo::RowArgsV& args, int64_t T,
@@ -379,7 +382,7 @@ dppo_status logprob_fwd(const void* logits, int32_t dtype, int64_t T, int64_t V,
   const bool aligned = aligned16(logits) && ((ld * es) % 16 == 0);
   dppo::RowLaunch L = dppo::select_row_kernel(dtype, V, aligned, false, g_path_policy,
                                               ((uintptr_t)logits & (uintptr_t)(es - 1)) == 0);
-  cover_short_rows(L, T * V * es, false);
+  cover_short_rows(L, T * V * es, false, false);
   dppo::RowArgsV a{};
   a.logits = logits;
   a.ld = ld;
@@ -418,7 +421,7 @@ dppo_status logprob_fwd_versioned(const void* const* logits, int32_t K, int32_t 
     entry_aligned = entry_aligned && ((uintptr_t)logits[v] & (uintptr_t)(es - 1)) == 0;
   }
   dppo::RowLaunch L = dppo::select_row_kernel(dtype, V, aligned, false, g_path_policy, entry_aligned);
-  cover_short_rows(L, T * V * es, false);
+  cover_short_rows(L, T * V * es, false, false);
   // Rows gathered from several versions' logits want every slot of the device: at
   // 1024 x 19 (bf16, V = 151936, 4 versions) 32 of 32 slots took 0.753-0.757 ms against
   // 0.762-0.768 ms with the 30 that suit one matrix (same-box sweep).
@@ -469,7 +472,6 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
         (!dlogits || ((((uintptr_t)dlogits - (uintptr_t)logits) & 15) == 0 &&
                       ((ld_dlogits - ld) * es) % 16 == 0));
     L = dppo::select_row_kernel(dtype, V, aligned, dlogits != nullptr, g_path_policy, phase_ok);
-    cover_short_rows(L, T * V * es, true);
   }
   // Count mode: a persistent row kernel that can (RowLaunch::counts), on a batch short enough for
   // every workgroup to read the mask, counts the valid tokens itself, so prep_stats does not
@@ -481,6 +483,7 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
   // slower.
   const bool flag_counts = T > 0 && flags_out != nullptr && L.flag_counts &&
                            !(g_path_policy & kPolicyAtomicCounts);
+  cover_short_rows(L, T * V * es, true, flag_counts);
   const bool count_mode = flag_counts && T <= dppo::kCountModeMaxT && L.persistent && L.counts;
   hipError_t e = hipSuccess;
   if (!count_mode) {

@@ -797,3 +797,39 @@ def test_autograd_backward_of_a_lazily_negated_gradient():
     a = torch.autograd.grad(loss, (h, w), u, retain_graph=True)
     b = torch.autograd.grad(loss, (h, w), u.clone())
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("dtype,T,grads", [(torch.bfloat16, 262144, True), (torch.float32, 131072, False)])
+def test_short_rows_without_flags_do_not_queue_on_the_counters(dtype, T, grads):
+    """A large batch of short rows takes about as long without flags as with them (1.04 times with
+    gradients, 1.2 forward only; a workgroup for every four rows, each ending in counter atomics,
+    took 6.5 and 7.4 times), and counts the same."""
+    V = 1024
+    _say("short rows without flags", dtype, T)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    z = torch.randn(T, V, generator=g, device=DEV).to(dtype)
+    ids = torch.randint(0, V, (T,), generator=g, device=DEV)
+    lp = P.logprob_fwd(z, ids)
+    adv = torch.randn(T, generator=g, device=DEV)
+    d = torch.empty_like(z) if grads else None
+
+    def call(flags):
+        return P.decoupled_ppo_loss_fwd_bwd(z, ids, lp, lp, adv, dlogits=d, want_dlogits=grads,
+                                            want_flags=flags)
+
+    def ms(flags):
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                call(flags)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[3]
+
+    a, b = call(True), call(False)
+    assert torch.equal(a.stats, b.stats) and torch.equal(a.loss, b.loss)
+    with_flags, without = ms(True), ms(False)
+    assert without < 2.5 * with_flags, (without, with_flags)
