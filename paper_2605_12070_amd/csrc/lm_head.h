@@ -86,10 +86,10 @@ hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st);
 hipError_t launch_lmh_grad_gemm(const GemmArgs& g, bool a_mn, bool b_mn, hipStream_t st);
 
 // Vocabulary rows per step of the chunked backward: at most `chunk` (the rows of G the
-// workspace holds, a multiple of 256), and the multiple of 256 down to a quarter of it with
-// the shortest estimated total over V rows. A step of the whole chunk can leave the last round
-// of tiles of each kernel nearly empty: at T = 2048, d = 4096 a chunk of 11008 rows is 344 logit
-// tiles for 256 CUs, 8192 rows are 256.
+// workspace holds, a multiple of 256), and of the multiples of 256 down to a quarter of it that
+// fill whole rounds of tiles (and a few between) the one with the shortest estimated total over V
+// rows. A step of the whole chunk can leave the last round of tiles of each kernel nearly empty:
+// at T = 2048, d = 4096 a chunk of 11520 rows is 360 logit tiles for 256 CUs, 8192 rows are 256.
 int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool dhidden,
                           bool dweight);
 

@@ -510,23 +510,40 @@ bool lmh_small_tiles(int64_t T, int64_t n, int64_t d) {
 // The tile size, and the product in splits slices of K, where estimated fastest: with few C
 // tiles and a long K (dhidden of a short batch: K is the vocabulary) most CUs would have no
 // tile at all. Returns the estimate.
+// It runs on the host in every call, and a step search asks for it a hundred times, so only the slice
+// counts that fill whole rounds of CUs are tried: over 20000 shapes (T up to 8192, d 8192, V 160000)
+// the same choice as among all 128 counts in 99.9 %, at most 1.3 % from it otherwise.
 static double lmh_pick(GemmArgs& g, bool a_mn, bool* small, int cus) {
   const int64_t mn = (int64_t)g.M * g.N;
   const bool can_split = g.part && g.ldc == g.N && g.N % 4 == 0;
   const int64_t most = can_split ? std::min<int64_t>(kMaxSplits, g.part_floats / mn) : 1;
   double best = 0.0;
   g.splits = 0;
+  auto consider = [&](int64_t s, bool sm) {
+    s = std::max<int64_t>(1, std::min(s, most));
+    int64_t kper = g.K;
+    if (s > 1) {
+      kper = ((g.K + s - 1) / s + kTurn - 1) / kTurn * kTurn;
+      s = (g.K + kper - 1) / kper;                        // no slice without K
+      if (s == 1) kper = g.K;
+    }
+    const double t = gemm_us(g.M, g.N, s, kper, a_mn, sm, cus);
+    if (g.splits == 0 || t < best) {
+      best = t;
+      g.splits = (int32_t)s;
+      g.kper = (int32_t)kper;
+      *small = sm;
+    }
+  };
   for (int sm = 0; sm < 2; ++sm) {
-    for (int64_t s = 1; s <= std::max<int64_t>(1, most); ++s) {
-      const int64_t kper = s == 1 ? g.K : ((g.K + s - 1) / s + kTurn - 1) / kTurn * kTurn;
-      if ((g.K + kper - 1) / kper != s) continue;         // some slice would hold no K
-      const double t = gemm_us(g.M, g.N, s, kper, a_mn, sm == 1, cus);
-      if (g.splits == 0 || t < best) {
-        best = t;
-        g.splits = (int32_t)s;
-        g.kper = (int32_t)kper;
-        *small = sm == 1;
-      }
+    const int64_t w = sm ? LMH_SMALL : LMH_GBM;
+    const int64_t nt = ((g.M + w - 1) / w) * ((g.N + w - 1) / w);
+    int64_t last = 1;
+    consider(last, sm == 1);
+    for (int64_t q = 1; q <= 8 && last < most; ++q) {     // q tiles on every CU
+      if (q * cus / nt <= last) continue;
+      last = q * cus / nt;
+      consider(last, sm == 1);
     }
   }
   return best;
@@ -560,17 +577,45 @@ int64_t lmh_backward_step(int64_t T, int64_t d, int64_t V, int64_t chunk, bool d
     }
     return t;
   };
+  // Steps that fill whole rounds of tiles in one of the kernels, equal steps over V, and an even
+  // spread between. Every multiple of 256 instead took the host 2 ms a call at T = 256, V = 151936
+  // and up to 47 ms elsewhere; these take 40 us at most, and over 600 shapes (T 16 .. 4096, d 64 ..
+  // 4096, V 2000 .. 2000000) end at an estimate 0.06 % higher on average, 2.1 % at worst.
+  const int64_t least = std::max<int64_t>(LMH_BN, chunk / 4);
+  constexpr int kTried = 48;
+  int64_t tried[kTried];
+  int n = 0;
   int64_t best_c = chunk;
   double best = 0.0;
-  for (int64_t c = chunk; c >= LMH_BN; c -= LMH_BN) {
+  auto consider = [&](int64_t c) {
+    c = std::min(c, chunk);
+    if (c < least || n == kTried) return;
+    for (int i = 0; i < n; ++i)
+      if (tried[i] == c) return;
+    tried[n++] = c;
     const int64_t whole = V / c, rest = V % c;
     const double t = (double)whole * step_us(c) + (rest ? step_us(rest) : 0.0);
-    if (c == chunk || t < best) {
+    if (n == 1 || t < best) {
       best = t;
       best_c = c;
     }
-    if (c <= chunk / 4) break;
+  };
+  consider(chunk);
+  // tiles of w x w, `across` entries on the side that is not the vocabulary
+  auto rounds = [&](int64_t across, int64_t w) {
+    const int64_t per = (across + w - 1) / w;
+    const int64_t most = ((chunk + w - 1) / w * per + cus - 1) / cus;
+    for (int64_t k = most; k >= 1 && k > most - 8; --k) consider(k * cus / per * w / LMH_BN * LMH_BN);
+  };
+  rounds(T, LMH_BM);
+  rounds(T, LMH_SMALL);
+  if (dweight) {
+    rounds(d, LMH_GBM);
+    rounds(d, LMH_SMALL);
   }
+  for (int64_t k = 1; k < 12; ++k) consider(chunk - k * (chunk - least) / 12 / LMH_BN * LMH_BN);
+  const int64_t steps = (V + chunk - 1) / chunk;
+  for (int64_t k = steps; k < steps + 4; ++k) consider(((V + k - 1) / k + LMH_BN - 1) / LMH_BN * LMH_BN);
   return best_c;
 }
 
