@@ -6,6 +6,8 @@
 //   scale_to_bf16  a float32 gradient times g, rounded once to bf16.
 // Both are HBM-bound streams with one 16-byte store per thread over many small workgroups, the
 // shape in which a read-write stream moves the most bytes per second on MI355X.
+#include <algorithm>
+
 #include "dppo.h"
 #include "dppo_device.h"
 #include "grad_scale.h"
@@ -15,7 +17,7 @@ namespace dppo {
 constexpr int kScaleNT = 512;
 
 // Workgroups [row * per_row, (row + 1) * per_row) cover row `row`. Rows may start anywhere (d
-// and out are contiguous and both on a 16-byte boundary, so they share every row's phase):
+// and out are contiguous and at the same offset within 16 bytes, so they share every row's phase):
 // chunks are the 16-byte blocks of memory the row touches, the first and last entry by entry.
 template <bool BF16>
 __global__ __launch_bounds__(kScaleNT) void scale_rows(ScaleRowsArgs a, int per_row) {
@@ -79,24 +81,43 @@ __global__ __launch_bounds__(256) void scale_to_bf16(const float* src, uint16_t*
   for (int64_t e = i; e < n; ++e) dst[e] = to_bf16(src[e] * g);
 }
 
-hipError_t launch_scale_rows(const ScaleRowsArgs& a, bool bf16, hipStream_t st) {
-  if (a.T <= 0) return hipSuccess;
+// A dispatch holds fewer than 2^32 threads (a grid that passes them is cut to 32 bits, with no
+// error): what exceeds them goes in several launches.
+constexpr int64_t kMaxThreads = 0xffffffff;
+
+hipError_t launch_scale_rows(const ScaleRowsArgs& a0, bool bf16, hipStream_t st) {
+  ScaleRowsArgs a = a0;
   const int64_t E = bf16 ? 8 : 4;
   const int64_t chunks = (a.V + 2 * E - 2) / E;      // at any phase
   const int64_t per_row = (chunks + kScaleNT - 1) / kScaleNT;
-  if (per_row * a.T > 0x7fffffff) return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)(per_row * a.T);
-  if (bf16) scale_rows<true><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
-  else scale_rows<false><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
-  return hipGetLastError();
+  const int64_t most = kMaxThreads / kScaleNT / per_row;   // 8 rows or more: V < 2^31
+  for (int64_t t0 = 0; t0 < a0.T; t0 += most) {
+    const int64_t off = t0 * a.V * (16 / E);
+    a.d = (const char*)a0.d + off;
+    a.out = (char*)a0.out + off;
+    if (a0.flags) {
+      a.flags = a0.flags + t0;
+      a.loss_tok = a0.loss_tok + t0;
+    }
+    a.T = (int32_t)std::min(most, a0.T - t0);
+    const unsigned grid = (unsigned)(per_row * a.T);
+    if (bf16) scale_rows<true><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
+    else scale_rows<false><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_scale_to_bf16(const float* src, void* dst, int64_t n, const float* g, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = ((n + 7) / 8 + 255) / 256;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  scale_to_bf16<<<(unsigned)blocks, 256, 0, st>>>(src, (uint16_t*)dst, n, g);
-  return hipGetLastError();
+  constexpr int64_t most = kMaxThreads / 256 * 256 * 8;
+  for (int64_t i = 0; i < n; i += most) {
+    const int64_t m = std::min(most, n - i);
+    scale_to_bf16<<<(unsigned)((m + 2047) / 2048), 256, 0, st>>>(src + i, (uint16_t*)dst + i, m, g);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dppo

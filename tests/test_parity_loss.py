@@ -833,3 +833,17 @@ def test_short_rows_without_flags_do_not_queue_on_the_counters(dtype, T, grads):
     assert torch.equal(a.stats, b.stats) and torch.equal(a.loss, b.loss)
     with_flags, without = ms(True), ms(False)
     assert without < 2.5 * with_flags, (without, with_flags)
+
+
+def test_scaled_gradient_past_a_dispatchs_threads():
+    """The backward's scale pass over more threads than the 2^32 a dispatch holds: every entry is
+    scaled once. (At V = 151936 that is from 220753 tokens on.)"""
+    T, V = 4194307, 4097                     # two workgroups of 512 threads a row, 34 GB
+    _say("scale pass past a dispatch", T, V)
+    d = torch.empty(T, V, dtype=torch.bfloat16, device=DEV)
+    d.fill_(2.0)
+    u = torch.tensor(0.25, device=DEV)
+    P._lib.check(P._lib.lib().dppo_scale_dlogits(d.data_ptr(), P._dtype_code(d), T, V, None, None, 3, u.data_ptr(),
+                                                 d.data_ptr(), torch.cuda.current_stream().cuda_stream), "scale")
+    low, high = torch.aminmax(d)
+    assert low.item() == 0.5 and high.item() == 0.5
