@@ -5,6 +5,7 @@ Every case prints its name, shape and seed before it touches the GPU.
 import json
 import math
 import os
+import time
 
 import numpy as np
 import pytest
@@ -833,6 +834,29 @@ def test_short_rows_without_flags_do_not_queue_on_the_counters(dtype, T, grads):
     assert torch.equal(a.stats, b.stats) and torch.equal(a.loss, b.loss)
     with_flags, without = ms(True), ms(False)
     assert without < 2.5 * with_flags, (without, with_flags)
+
+
+def test_more_short_rows_than_a_dispatch_has_threads_for():
+    """2^26 + 5 rows, one wave each: a grid that covers them passes 2^32 threads, which a dispatch
+    cannot hold; cut to 32 bits it left two workgroups to loop over all rows, 15 s a call against
+    tens of milliseconds. Log-probs, and the loss with gradients, of two-entry rows whose values
+    are known."""
+    T, V = (1 << 26) + 5, 2
+    _say("rows past a dispatch", T)
+    z = torch.zeros(T, V, dtype=torch.bfloat16, device=DEV)
+    ids = torch.zeros(T, dtype=torch.int64, device=DEV)
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    lp = P.logprob_fwd(z, ids)
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start < 2.0
+    want = -float(np.log(2.0))
+    assert torch.all((lp - want).abs() <= 2e-6)
+    adv = torch.ones(T, device=DEV)
+    r = P.decoupled_ppo_loss_fwd_bwd(z, ids, lp, lp, adv, dlogits=z, scale_mode="const", want_flags=True)
+    assert r.stats.tolist() == [T, T, T, T, 0]
+    assert torch.all(z[:, 0] == -0.5) and torch.all(z[:, 1] == 0.5)   # w (p - 1), w p
+    assert abs(r.loss.item() + T) <= 1e-5 * T
 
 
 def test_scaled_gradient_past_a_dispatchs_threads():
