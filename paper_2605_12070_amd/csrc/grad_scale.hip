@@ -16,52 +16,58 @@ namespace dppo {
 
 constexpr int kScaleNT = 512;
 
-// Workgroups [row * per_row, (row + 1) * per_row) cover row `row`. Rows may start anywhere (d
-// and out are contiguous and at the same offset within 16 bytes, so they share every row's phase):
-// chunks are the 16-byte blocks of memory the row touches, the first and last entry by entry.
+// Whether row `row` of dlogits holds anything but zeros, by the loss call's flags.
+__device__ __forceinline__ bool row_live(const ScaleRowsArgs& a, int64_t row) {
+  const uint32_t fl = a.flags[row];
+  const float lt = a.loss_tok[row];
+  const bool active = (fl & DPPO_FLAG_PPO) && ((fl & DPPO_FLAG_BAND) || !a.uses_band);
+  return active || lt != lt;                     // a NaN row's gradient is NaN, not zero
+}
+
 template <bool BF16>
-__global__ __launch_bounds__(kScaleNT) void scale_rows(ScaleRowsArgs a, int per_row) {
-  constexpr int ES = BF16 ? 2 : 4;
-  constexpr int E = 16 / ES;
-  const int64_t row = blockIdx.x / per_row;
-  const int c = (int)(blockIdx.x % per_row) * kScaleNT + threadIdx.x;
-  const char* src = (const char*)a.d + row * a.V * ES;
-  char* dst = (char*)a.out + row * a.V * ES;
-  const int ph = (int)(((uintptr_t)src & 15) / ES);
-  const int e0 = c * E - ph;                     // the chunk's first entry, within the row
-  if (e0 >= a.V) return;
-  // the upstream gradient in dlogits' type, as a product of two tensors of that type takes it
+__device__ __forceinline__ u32x4 scaled(const u32x4& v, float g) {
+  u32x4 o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (BF16) o[k] = pack_bf16(bf16_lo(v[k]) * g, bf16_hi(v[k]) * g);
+    else o[k] = __float_as_uint(__uint_as_float(v[k]) * g);
+  }
+  return o;
+}
+
+// dlogits as one run of 16-byte chunks, whatever rows they lie in (both buffers start on a 16-byte
+// boundary), one chunk per thread over the n entries from row 0 on; a chunk is read if any row it
+// touches is live. Against whole workgroups for each row, which leave threads idle at every row's
+// end, and against torch's product (us, every row live): T = 1M, V = 1 bf16 3.9, 561, 10.4;
+// T = 262144, V = 100 20, 207, 21; T = 65536, V = 1000 43, 56, 43; V = 4001 164, 213, 182; T = 32768,
+// V = 6000 124, 161, 136; V = 8192 168, 169, 184; T = 16384, V = 32000, 40 % masked 284, 294, 355.
+template <bool BF16>
+__global__ __launch_bounds__(kScaleNT) void scale_rows(ScaleRowsArgs a, int64_t n) {
+  constexpr int E = BF16 ? 8 : 4;
+  const int64_t e0 = (int64_t)blockIdx.x * (kScaleNT * E);
+  const int64_t at = e0 + (int)threadIdx.x * E;
+  if (at >= n) return;
   float g = uload(a.g);
   if (BF16) g = bf16_to_f32(to_bf16(g));
-  bool live = true;                              // uniform over the workgroup
-  if (a.flags != nullptr) {
-    const uint32_t fl = a.flags[row];
-    const float lt = a.loss_tok[row];
-    const bool active = (fl & DPPO_FLAG_PPO) && ((fl & DPPO_FLAG_BAND) || !a.uses_band);
-    live = active || lt != lt;                   // a NaN row's gradient is NaN, not zero
+  bool live = a.flags == nullptr;
+  if (!live) {
+    const uint32_t V = (uint32_t)a.V;
+    const int64_t row0 = e0 / a.V;               // uniform over the workgroup
+    // entries from row0's start: less than V + kScaleNT E
+    const uint32_t first = (uint32_t)(e0 - row0 * a.V) + threadIdx.x * E;
+    const uint32_t last = first + (uint32_t)(n - at < E ? n - at : E) - 1;
+    const uint32_t r1 = last / V;
+    for (uint32_t r = first / V; r <= r1; ++r) live = live || row_live(a, row0 + r);
   }
-  if (e0 >= 0 && e0 + E <= a.V) {
+  if (at + E <= n) {
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (live) v = __builtin_nontemporal_load((const u32x4*)(src + (int64_t)e0 * ES));
-    u32x4 o;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (BF16) o[k] = pack_bf16(bf16_lo(v[k]) * g, bf16_hi(v[k]) * g);
-      else o[k] = __float_as_uint(__uint_as_float(v[k]) * g);
-    }
-    __builtin_nontemporal_store(o, (u32x4*)(dst + (int64_t)e0 * ES));
+    if (live) v = __builtin_nontemporal_load((const u32x4*)a.d + at / E);
+    __builtin_nontemporal_store(scaled<BF16>(v, g), (u32x4*)a.out + at / E);
     return;
   }
-  for (int j = 0; j < E; ++j) {
-    const int e = e0 + j;
-    if (e < 0 || e >= a.V) continue;
-    if (BF16) {
-      const float x = live ? bf16_to_f32(((const uint16_t*)src)[e]) : 0.0f;
-      ((uint16_t*)dst)[e] = to_bf16(x * g);
-    } else {
-      const float x = live ? ((const float*)src)[e] : 0.0f;
-      ((float*)dst)[e] = x * g;
-    }
+  for (int64_t e = at; e < n; ++e) {
+    if (BF16) ((uint16_t*)a.out)[e] = to_bf16(live ? bf16_to_f32(((const uint16_t*)a.d)[e]) * g : 0.0f * g);
+    else ((float*)a.out)[e] = live ? ((const float*)a.d)[e] * g : 0.0f * g;
   }
 }
 
@@ -88,9 +94,8 @@ constexpr int64_t kMaxThreads = 0xffffffff;
 hipError_t launch_scale_rows(const ScaleRowsArgs& a0, bool bf16, hipStream_t st) {
   ScaleRowsArgs a = a0;
   const int64_t E = bf16 ? 8 : 4;
-  const int64_t chunks = (a.V + 2 * E - 2) / E;      // at any phase
-  const int64_t per_row = (chunks + kScaleNT - 1) / kScaleNT;
-  const int64_t most = kMaxThreads / kScaleNT / per_row;   // 8 rows or more: V < 2^31
+  // rows of a launch, a multiple of E so that the next starts on a chunk: 8 or more (V < 2^31)
+  const int64_t most = kMaxThreads / kScaleNT * kScaleNT * E / a.V / E * E;
   for (int64_t t0 = 0; t0 < a0.T; t0 += most) {
     const int64_t off = t0 * a.V * (16 / E);
     a.d = (const char*)a0.d + off;
@@ -100,9 +105,10 @@ hipError_t launch_scale_rows(const ScaleRowsArgs& a0, bool bf16, hipStream_t st)
       a.loss_tok = a0.loss_tok + t0;
     }
     a.T = (int32_t)std::min(most, a0.T - t0);
-    const unsigned grid = (unsigned)(per_row * a.T);
-    if (bf16) scale_rows<true><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
-    else scale_rows<false><<<grid, kScaleNT, 0, st>>>(a, (int)per_row);
+    const int64_t n = a.T * (int64_t)a.V;
+    const unsigned grid = (unsigned)(((n + E - 1) / E + kScaleNT - 1) / kScaleNT);
+    if (bf16) scale_rows<true><<<grid, kScaleNT, 0, st>>>(a, n);
+    else scale_rows<false><<<grid, kScaleNT, 0, st>>>(a, n);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -861,8 +861,8 @@ def test_more_short_rows_than_a_dispatch_has_threads_for():
 
 def test_scaled_gradient_past_a_dispatchs_threads():
     """The backward's scale pass over more threads than the 2^32 a dispatch holds: every entry is
-    scaled once. (At V = 151936 that is from 220753 tokens on.)"""
-    T, V = 4194307, 4097                     # two workgroups of 512 threads a row, 34 GB
+    scaled once. (At V = 151936 that is from 226147 tokens on.)"""
+    T, V = 4194307, 8200                     # 2^32 threads of 8 entries and some more, 69 GB
     _say("scale pass past a dispatch", T, V)
     d = torch.empty(T, V, dtype=torch.bfloat16, device=DEV)
     d.fill_(2.0)
@@ -871,3 +871,55 @@ def test_scaled_gradient_past_a_dispatchs_threads():
                                                  d.data_ptr(), torch.cuda.current_stream().cuda_stream), "scale")
     low, high = torch.aminmax(d)
     assert low.item() == 0.5 and high.item() == 0.5
+
+
+@pytest.mark.parametrize("T,V", [(1, 1), (4099, 1), (1500, 3), (1029, 7), (700, 9), (33, 4095), (5, 12289)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_scale_pass_over_rows_shorter_than_a_chunk(dtype, T, V):
+    """The backward's scale pass runs over 16-byte chunks whatever rows they lie in: several rows to a
+    chunk, a chunk over two rows, one workgroup over many rows, a last chunk that is not whole. Rows
+    that the flags call zero become zero, NaN rows (by their loss) stay, and nothing past the end is
+    written."""
+    _say("scale pass, short rows", dtype, T, V)
+    g = torch.Generator(device=DEV).manual_seed(T * V)
+    d = torch.randn(T, V, generator=g, device=DEV).to(dtype)
+    flags = torch.randint(0, 8, (T,), generator=g, device=DEV, dtype=torch.uint8)
+    loss_tok = torch.zeros(T, device=DEV)
+    nan = torch.rand(T, generator=g, device=DEV) < 0.1
+    loss_tok[nan], flags[nan], d[nan] = float("nan"), P.FLAG_VALID, float("nan")
+    both = P.FLAG_BAND | P.FLAG_PPO
+    dead = ((flags & both) != both) & ~nan
+    d[dead] = 0
+    buf = torch.full((T * V + 64,), 9.0, device=DEV).to(dtype)
+    out = buf[:T * V].view(T, V)
+    u = torch.tensor(-0.7, device=DEV)
+    P._lib.check(P._lib.lib().dppo_scale_dlogits(
+        d.data_ptr(), P._dtype_code(d), T, V, flags.data_ptr(), loss_tok.data_ptr(), P.RD_MODES["mask_weight"],
+        u.data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream), "scale")
+    want = d * u.to(dtype)
+    assert torch.equal(out.nan_to_num(7.0), want.nan_to_num(7.0)) and torch.equal(out.isnan(), want.isnan())
+    assert torch.all(buf[T * V:] == 9.0)
+
+
+def test_scale_pass_of_short_rows_keeps_pace_with_a_product():
+    """A million rows of 16 entries: no slower than twice torch's product (a workgroup for each row
+    took 35 times as long)."""
+    T, V = 1 << 20, 16
+    d = torch.randn(T, V, device=DEV).to(torch.bfloat16)
+    out, u = torch.empty_like(d), torch.tensor(0.5, device=DEV)
+    L, st = P._lib.lib(), torch.cuda.current_stream().cuda_stream
+
+    def us(f):
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        return sorted(times)[3]
+
+    here = us(lambda: L.dppo_scale_dlogits(d.data_ptr(), 1, T, V, None, None, 3, u.data_ptr(), out.data_ptr(), st))
+    assert here < 2 * us(lambda: torch.mul(d, u, out=out)), here
