@@ -740,7 +740,10 @@ __device__ __forceinline__ void resident_rows(const RowArgsOf<BWD>& a) {
   } else {
     for (; row < a.T; row += gridDim.x) step(r1, r1, x1, x1, false);
   }
-  if (threadIdx.x == 0 && !(DB && a.count_mode)) add_stats(a, sc);
+  if (threadIdx.x == 0) {
+    if constexpr (DB) flush_stats(a, sc);
+    else add_stats(a, sc);                 // RowLaunch::flag_counts is false: the counters' only source
+  }
 }
 
 template <int NT, int NC, bool BWD>

@@ -103,8 +103,8 @@ __device__ __forceinline__ float row_scale(const RowArgs& a) {
 
 // A workgroup's counters, kept by thread 0 over all of its rows and added to the global
 // counters once, when the workgroup ends: device-scope atomics on the same five addresses
-// serialise, and one per row made a batch of short rows wait on them. In a call that writes
-// flags nothing is added here: loss_sum derives the counters from them.
+// serialise, and one per row made a batch of short rows wait on them. With RowArgs::flag_counts
+// nothing is added here: loss_sum derives the counters from the flags.
 struct StatCount {
   int band = 0, ppo = 0, active = 0, bad = 0;
 };

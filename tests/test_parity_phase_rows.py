@@ -340,7 +340,12 @@ def test_short_rows_one_wave_each(dtype, T, V, extra, off):
 
 @pytest.mark.parametrize("dtype,T,V,grads", [("bf16", 1027, 700, True), ("bf16", 1027, 9001, False),
                                              ("bf16", 515, 160001, True), ("f32", 1027, 700, True),
-                                             ("f32", 515, 30001, True), ("f32", 515, 90001, False)])
+                                             ("f32", 515, 30001, True), ("f32", 515, 90001, False),
+                                             # batches long enough that the counters come from
+                                             # atomics: past 65536 tokens, forward past 16384
+                                             ("bf16", 65601, 12296, True), ("bf16", 65601, 12297, True),
+                                             ("f32", 65601, 6150, True), ("bf16", 16384, 12296, False),
+                                             ("bf16", 16385, 12296, False)])
 def test_counters_from_flags_and_from_atomics(dtype, T, V, grads):
     """The counters and the loss are the same whether loss_sum derives them from the flags or the
     kernels add them (no flags written, or the atomics policy)."""
