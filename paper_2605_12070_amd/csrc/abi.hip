@@ -483,7 +483,15 @@ dppo_status decoupled_ppo_loss_fwd_bwd(
   // bf16 63 us with 1512 workgroups' atomics. The single-buffer bf16 gradient kernels of long
   // rows keep theirs (few workgroups): the test at their end made the 1024 x 19 kernel 1.5 %
   // slower.
+  // So does a persistent grid of workgroups per row on a batch too long for count mode (a quarter of
+  // that without one): loss_sum, a single workgroup, would read another byte per token. Atomics
+  // against flags: forward and backward T = 131072, V = 12800 bf16 1412 / 1438 us, T = 262144,
+  // V = 8000 fp32 3467 / 3521; forward T = 262144, V = 12800 bf16 1937 / 1998, T = 65536, V = 16000
+  // 491 / 507, T = 32768 254 / 258, T = 16384 135 / 135, T = 4096 55 / 44.
+  const bool few_groups = L.persistent && L.rows_per_group == 1;
+  const int64_t flags_most = L.counts ? dppo::kCountModeMaxT : dppo::kCountModeMaxT / 4;
   const bool flag_counts = T > 0 && flags_out != nullptr && L.flag_counts &&
+                           (T <= flags_most || !few_groups) &&
                            !(g_path_policy & kPolicyAtomicCounts);
   cover_short_rows(L, T * V * es, true, flag_counts);
   const bool count_mode = flag_counts && T <= dppo::kCountModeMaxT && L.persistent && L.counts;
