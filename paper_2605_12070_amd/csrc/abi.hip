@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "dppo.h"
+#include "dppo_device.h"
 #include "ewma.h"
 #include "grad_scale.h"
 #include "lm_head.h"
@@ -132,8 +133,8 @@ dppo_status launch_rows(const dppo::RowLaunch& L, const dppo::RowArgsV& args, in
     if (slots < 1) slots = 1;
     if (slots < grid) grid = slots;
   }
-  // A dispatch holds fewer than 2^32 threads; every row kernel loops over the rows past its grid.
-  grid = std::min(grid, (int64_t)0xffffffff / L.threads);
+  // every row kernel loops over the rows past its grid
+  grid = std::min(grid, dppo::kLaunchThreads / L.threads);
   dppo::RowArgsV a = args;
   a.stagger = L.stagger;
   auto* ev = timer_slot();

@@ -14,6 +14,10 @@
 
 namespace dppo {
 
+// A dispatch holds fewer than 2^32 threads; a grid that passes them is cut to 32 bits, with no
+// error. What exceeds this half of them goes in several launches.
+constexpr int64_t kLaunchThreads = (int64_t)1 << 31;
+
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr uint32_t kBf16NegInfPair = 0xFF80FF80u;  // two bf16 -inf

@@ -3,6 +3,8 @@
 // on the device together with the reset rule of Sec. 5.2 (ewma_controller). b = 0 means
 // the old contents are not read (first step, reset). HBM-bound: one 16-byte vector per
 // thread, float32 arithmetic, bf16 storage rounded to nearest even.
+#include <algorithm>
+
 #include "dppo.h"
 #include "dppo_device.h"
 #include "ewma.h"
@@ -174,34 +176,35 @@ __global__ __launch_bounds__(1024) void ewma_step_group(void* xp_, const void* x
   }
 }
 
+namespace {
+// One thread per 16-byte vector (plus one per tail element), no grid-stride loop: on
+// MI355X this moves 6.1-6.3 TB/s on a 1 Gi-element fp32 buffer, against 4.9 TB/s for a
+// 2048-workgroup grid-stride loop and 5.7 TB/s for four vectors per thread.
+// go(grid, x_prox, x_new, n) launches one piece of the buffers.
+template <typename Go>
+hipError_t ewma_pieces(void* xp, const void* xn, bool bf16, int64_t n, bool aligned, Go&& go) {
+  const int64_t E = aligned ? (bf16 ? 8 : 4) : 1;
+  const int64_t es = bf16 ? 2 : 4;
+  const int64_t most = kLaunchThreads * E;
+  for (int64_t i = 0; i < n; i += most) {
+    const int64_t k = std::min(most, n - i);
+    go(dim3((unsigned)((k / E + k % E + 255) / 256)), (char*)xp + i * es, (const char*)xn + i * es, k);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+}  // namespace
+
 hipError_t launch_ewma(void* xp, const void* xn, bool bf16, int64_t n, float ca, float cb,
                        bool read_old, bool aligned, hipStream_t st) {
-  // One thread per 16-byte vector (plus one per tail element), no grid-stride loop: on
-  // MI355X this moves 6.1-6.3 TB/s on a 1 Gi-element fp32 buffer, against 4.9 TB/s for a
-  // 2048-workgroup grid-stride loop and 5.7 TB/s for four vectors per thread.
-  const int64_t E = aligned ? (bf16 ? 8 : 4) : 1;
-  const int64_t threads = n / E + n % E;
-  const int64_t blocks = (threads + 255) / 256;
-  if (blocks < 1 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)blocks), b(256);
-  if (aligned) {
-    if (bf16) {
-      if (read_old) ewma_kernel<true, true><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-      else ewma_kernel<true, false><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-    } else {
-      if (read_old) ewma_kernel<false, true><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-      else ewma_kernel<false, false><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-    }
-  } else {
-    if (bf16) {
-      if (read_old) ewma_kernel_scalar<true, true><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-      else ewma_kernel_scalar<true, false><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-    } else {
-      if (read_old) ewma_kernel_scalar<false, true><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-      else ewma_kernel_scalar<false, false><<<g, b, 0, st>>>(xp, xn, n, ca, cb);
-    }
-  }
-  return hipGetLastError();
+  auto* fn = aligned ? (bf16 ? (read_old ? ewma_kernel<true, true> : ewma_kernel<true, false>)
+                             : (read_old ? ewma_kernel<false, true> : ewma_kernel<false, false>))
+                     : (bf16 ? (read_old ? ewma_kernel_scalar<true, true> : ewma_kernel_scalar<true, false>)
+                             : (read_old ? ewma_kernel_scalar<false, true> : ewma_kernel_scalar<false, false>));
+  return ewma_pieces(xp, xn, bf16, n, aligned, [&](dim3 g, void* p, const void* q, int64_t k) {
+    fn<<<g, 256, 0, st>>>(p, q, k, ca, cb);
+  });
 }
 
 hipError_t launch_ewma_step(void* xp, const void* xn, bool bf16, int64_t n, float beta,
@@ -219,19 +222,13 @@ hipError_t launch_ewma_step(void* xp, const void* xn, bool bf16, int64_t n, floa
     return hipGetLastError();
   }
   ewma_controller<<<1, 64, 0, st>>>(stats, state, beta, tau, patience, normalized ? 1 : 0);
-  const int64_t E = aligned ? (bf16 ? 8 : 4) : 1;
-  const int64_t threads = n / E + n % E;
-  const int64_t blocks = (threads + 255) / 256;
-  if (blocks < 1 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)blocks), b(256);
-  if (aligned) {
-    if (bf16) ewma_kernel_dev<true><<<g, b, 0, st>>>(xp, xn, n, state);
-    else ewma_kernel_dev<false><<<g, b, 0, st>>>(xp, xn, n, state);
-  } else {
-    if (bf16) ewma_kernel_scalar_dev<true><<<g, b, 0, st>>>(xp, xn, n, state);
-    else ewma_kernel_scalar_dev<false><<<g, b, 0, st>>>(xp, xn, n, state);
-  }
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto* fn = aligned ? (bf16 ? ewma_kernel_dev<true> : ewma_kernel_dev<false>)
+                     : (bf16 ? ewma_kernel_scalar_dev<true> : ewma_kernel_scalar_dev<false>);
+  return ewma_pieces(xp, xn, bf16, n, aligned, [&](dim3 g, void* p, const void* q, int64_t k) {
+    fn<<<g, 256, 0, st>>>(p, q, k, state);
+  });
 }
 
 }  // namespace dppo

@@ -87,15 +87,11 @@ __global__ __launch_bounds__(256) void scale_to_bf16(const float* src, uint16_t*
   for (int64_t e = i; e < n; ++e) dst[e] = to_bf16(src[e] * g);
 }
 
-// A dispatch holds fewer than 2^32 threads (a grid that passes them is cut to 32 bits, with no
-// error): what exceeds them goes in several launches.
-constexpr int64_t kMaxThreads = 0xffffffff;
-
 hipError_t launch_scale_rows(const ScaleRowsArgs& a0, bool bf16, hipStream_t st) {
   ScaleRowsArgs a = a0;
   const int64_t E = bf16 ? 8 : 4;
-  // rows of a launch, a multiple of E so that the next starts on a chunk: 8 or more (V < 2^31)
-  const int64_t most = kMaxThreads / kScaleNT * kScaleNT * E / a.V / E * E;
+  // rows of a launch, a multiple of E so that the next starts on a chunk (V < 2^31: not zero)
+  const int64_t most = kLaunchThreads * E / a.V / E * E;
   for (int64_t t0 = 0; t0 < a0.T; t0 += most) {
     const int64_t off = t0 * a.V * (16 / E);
     a.d = (const char*)a0.d + off;
@@ -116,7 +112,7 @@ hipError_t launch_scale_rows(const ScaleRowsArgs& a0, bool bf16, hipStream_t st)
 }
 
 hipError_t launch_scale_to_bf16(const float* src, void* dst, int64_t n, const float* g, hipStream_t st) {
-  constexpr int64_t most = kMaxThreads / 256 * 256 * 8;
+  constexpr int64_t most = kLaunchThreads * 8;
   for (int64_t i = 0; i < n; i += most) {
     const int64_t m = std::min(most, n - i);
     scale_to_bf16<<<(unsigned)((m + 2047) / 2048), 256, 0, st>>>(src + i, (uint16_t*)dst + i, m, g);

@@ -9,6 +9,7 @@
 //   lmh_grad_scale turns the stored exponentials into G = w_t (softmax - onehot) in bf16,
 //                  the operand of the two gradient products (lm_head_grad.hip);
 //   lmh_bwd_tiles  vocabulary-chunk mode: recomputes a tile and writes G for one chunk.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -426,9 +427,9 @@ __global__ __launch_bounds__(64 * kTokWaves) void lmh_tokens(RowArgs a, LmhArgs 
 // workgroups is the shape in which a read-write stream moves the most bytes per second on
 // MI355X (as a per-row loop over four chunks per thread it took 1.0 ms at T = 8192,
 // V = 151936).
-__global__ __launch_bounds__(256) void lmh_grad_scale(LmhArgs m, int per_row) {
+__global__ __launch_bounds__(256) void lmh_grad_scale(LmhArgs m, int per_row, int64_t row0) {
   // per_row workgroups cover a row's chunks; consecutive workgroups walk along a row
-  const int64_t row = blockIdx.x / per_row;
+  const int64_t row = row0 + blockIdx.x / per_row;
   const int c = (int)(blockIdx.x % per_row) * 256 + threadIdx.x;
   if (c >= (int)(m.ldg / 8)) return;
   const int v0 = 8 * c;
@@ -529,12 +530,16 @@ hipError_t launch_lmh_tokens(const RowArgs& a, const LmhArgs& m, bool count, hip
 }
 
 hipError_t launch_lmh_grad_scale(const LmhArgs& m, hipStream_t st) {
-  if (m.ldg % 8 != 0 || m.ldg / 8 > 0x7fffffff) return hipErrorInvalidValue;
+  if (m.ldg % 8 != 0 || m.ldg > (1 << 21)) return hipErrorInvalidValue;
   if (m.T <= 0) return hipSuccess;
   const int64_t per_row = (m.ldg / 8 + 255) / 256;
-  if (per_row * m.T > 0x7fffffff) return hipErrorInvalidValue;
-  lmh_grad_scale<<<(unsigned)(per_row * m.T), 256, 0, st>>>(m, (int)per_row);
-  return hipGetLastError();
+  const int64_t most = kLaunchThreads / 256 / per_row;      // per_row <= 1024
+  for (int64_t r = 0; r < m.T; r += most) {
+    lmh_grad_scale<<<(unsigned)(per_row * std::min(most, m.T - r)), 256, 0, st>>>(m, (int)per_row, r);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_lmh_bwd_tiles(const LmhArgs& m, hipStream_t st) {
@@ -559,11 +564,13 @@ __global__ __launch_bounds__(256) void lmh_fill_zero(float* p, int64_t n) {
 }
 
 hipError_t launch_lmh_zero(float* p, int64_t n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  lmh_fill_zero<<<(unsigned)blocks, 256, 0, st>>>(p, n);
-  return hipGetLastError();
+  for (int64_t i = 0; i < n; i += kLaunchThreads) {
+    const int64_t k = std::min(kLaunchThreads, n - i);
+    lmh_fill_zero<<<(unsigned)((k + 255) / 256), 256, 0, st>>>(p + i, k);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dppo

@@ -11,6 +11,8 @@
 //                the same per-token values), then this shard's columns of
 //                dlogits = w (softmax - onehot).
 // 16-byte vector accesses on aligned rows.
+#include <algorithm>
+
 #include "dppo.h"
 #include "dppo_device.h"
 #include "loss_stage.h"
@@ -89,10 +91,10 @@ __device__ __forceinline__ void row_partial(const char* row, int Vs, float& N, f
 // One workgroup per row. (A persistent grid looping over rows measured 12-80 % slower for
 // this read-only kernel: every row's load, merge and barrier then run back to back.)
 template <bool BF16, bool VEC>
-__global__ __launch_bounds__(kNT) void shard_stats(ShardArgs s) {
+__global__ __launch_bounds__(kNT) void shard_stats(ShardArgs s, int64_t row0) {
   __shared__ float red[2 * (kNT / 64)];
   const RowArgs& a = s.a;
-  const int64_t row = blockIdx.x;
+  const int64_t row = row0 + blockIdx.x;
   constexpr int ES = BF16 ? 2 : 4;
   const bool valid = a.mask == nullptr || uload_u8(a.mask + row) != 0;
   if (!valid) {                        // not read: its statistics never reach a loss
@@ -253,15 +255,15 @@ __global__ __launch_bounds__(kNT) void shard_loss(ShardArgs s) {
 }
 
 hipError_t launch_shard_stats(const ShardArgs& s, bool bf16, bool vec, hipStream_t st) {
-  const dim3 g((unsigned)s.a.T), b(kNT);
-  if (bf16) {
-    if (vec) shard_stats<true, true><<<g, b, 0, st>>>(s);
-    else shard_stats<true, false><<<g, b, 0, st>>>(s);
-  } else {
-    if (vec) shard_stats<false, true><<<g, b, 0, st>>>(s);
-    else shard_stats<false, false><<<g, b, 0, st>>>(s);
+  constexpr int64_t most = kLaunchThreads / kNT;
+  auto* fn = bf16 ? (vec ? shard_stats<true, true> : shard_stats<true, false>)
+                  : (vec ? shard_stats<false, true> : shard_stats<false, false>);
+  for (int64_t r = 0; r < s.a.T; r += most) {
+    fn<<<(unsigned)std::min<int64_t>(most, s.a.T - r), kNT, 0, st>>>(s, r);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_shard_combine(const float* lse_s, int32_t P, int64_t T, float* lse, hipStream_t st) {
@@ -327,12 +329,12 @@ __global__ __launch_bounds__(256) void shard_token(ShardArgs s) {
 constexpr int kGradNT = 512;  // threads of a shard_grad workgroup (128-1024 measured)
 
 template <bool BF16>
-__global__ __launch_bounds__(kGradNT) void shard_grad(ShardArgs s, int per_row) {
+__global__ __launch_bounds__(kGradNT) void shard_grad(ShardArgs s, int per_row, int64_t row0) {
   __shared__ float rb[4];
   const RowArgs& a = s.a;
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int E = 16 / ES;
-  const int64_t row = blockIdx.x / per_row;
+  const int64_t row = row0 + blockIdx.x / per_row;
   const int c = (int)(blockIdx.x % per_row) * kGradNT + threadIdx.x;
   const int Vs = a.V;
   const int nfull = Vs / E;
@@ -398,11 +400,15 @@ hipError_t launch_shard_loss(const ShardArgs& s, bool bf16, bool vec, hipStream_
     if (e0 != hipSuccess) return e0;
     const int E = bf16 ? 8 : 4;
     const int64_t per_row = (s.a.V / E + kGradNT) / kGradNT;  // whole chunks, the tail thread
-    if (per_row * s.a.T > 0x7fffffff) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(per_row * s.a.T);
-    if (bf16) shard_grad<true><<<grid, kGradNT, 0, st>>>(s, (int)per_row);
-    else shard_grad<false><<<grid, kGradNT, 0, st>>>(s, (int)per_row);
-    return hipGetLastError();
+    const int64_t most = kLaunchThreads / kGradNT / per_row;  // a shard row is at most 1 GiB
+    for (int64_t r = 0; r < s.a.T; r += most) {
+      const unsigned grid = (unsigned)(per_row * std::min<int64_t>(most, s.a.T - r));
+      if (bf16) shard_grad<true><<<grid, kGradNT, 0, st>>>(s, (int)per_row, r);
+      else shard_grad<false><<<grid, kGradNT, 0, st>>>(s, (int)per_row, r);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   const void* fn = bf16 ? (vec ? (const void*)shard_loss<true, true> : (const void*)shard_loss<true, false>)
                         : (vec ? (const void*)shard_loss<false, true> : (const void*)shard_loss<false, false>);

@@ -871,6 +871,8 @@ def test_scaled_gradient_past_a_dispatchs_threads():
                                                  d.data_ptr(), torch.cuda.current_stream().cuda_stream), "scale")
     low, high = torch.aminmax(d)
     assert low.item() == 0.5 and high.item() == 0.5
+    del d
+    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("T,V", [(1, 1), (4099, 1), (1500, 3), (1029, 7), (700, 9), (33, 4095), (5, 12289)])
