@@ -306,12 +306,12 @@ def test_lm_head_autograd_wrapper_returns_the_call_gradients():
 
 
 
-@pytest.mark.parametrize("T,d,V", [(1, 8, 300), (5, 520, 33000), (67, 1032, 16500)])
+@pytest.mark.parametrize("T,d,V", [(1, 8, 300), (5, 520, 33000), (67, 1032, 16500), (3, 8, 65700)])
 def test_token_pass_edges_and_counters_without_flags(T, d, V):
     """The token pass (one wave per token, four tokens per workgroup): fewer tokens than a
-    workgroup holds, a remainder, more than 64 x 8 groups' worth of partials (V > 65536 / 2 is
-    one round of its loop, 33000 two loads per lane), d past one wave-wide step. The counters
-    are the same whether they come from the flags or, without flags, from atomics."""
+    workgroup holds, a remainder, several partials per lane (33000 entries are 258 groups of 128),
+    more than a round of its loop takes (64 x 8 groups, 65536 entries), d past one wave-wide step.
+    The counters are the same whether they come from the flags or, without flags, from atomics."""
     wl, res, _ = _run(T, d, V, seed=40 + T, bad_ids=(0,) if T > 1 else ())
     lp_ref = res.logp.nan_to_num() - 0.1
     a = P.fused_lm_head_loss_fwd_bwd(wl.hidden, wl.weight, wl.ids, lp_ref, lp_ref, wl.adv, wl.mask)
