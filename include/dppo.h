@@ -30,11 +30,12 @@
  *    read as the aligned 16-byte chunks that cover them: the logits allocation must be readable
  *    from the 16-byte boundary at or below the first row to the one after the last row (true of
  *    any hipMalloc or PyTorch allocation, and of views into one). Of fp32 rows only their own
- *    entries are read, and of dlogits only the rows' own entries are written. Rows that are not aligned take the resident and prefix kernels when dlogits
- *    (if any) lies at the logits' offset within 16 bytes on every row (the same pointer residue
- *    mod 16 and strides that differ by a multiple of 16 bytes, as in place or for a tensor of
- *    the logits' layout). Other layouts, and forward calls on rows longer than the resident
- *    kernels hold, take a streaming path; none of this is an error.
+ *    entries are read, and of dlogits only the rows' own entries are written.
+ *  - Rows that are not aligned take the resident and prefix kernels when dlogits (if any) lies at
+ *    the logits' offset within 16 bytes on every row (the same pointer residue mod 16 and strides
+ *    that differ by a multiple of 16 bytes, as in place or for a tensor of the logits' layout).
+ *    Other layouts, and forward calls on rows longer than the resident kernels hold, take a
+ *    streaming path; none of this is an error.
  *  - Thread safety: calls may be issued from several host threads; the kernel timer
  *    (dppo_timer_*) is process-global and meant for one profiling thread.
  */

@@ -167,8 +167,9 @@ struct Operand {
   }
 };
 
-// Fragment reads of one operand for the wave's G 32-row tiles at tile offset wo (0 or 32 G). K-major: one 16-byte read per fragment. MN-major: two transposing 8-byte reads,
-// K 0..3 and 4..7 of the lane's eight.
+// Fragment reads of one operand for the wave's G 32-row tiles at tile offset wo (0 or 32 G).
+// K-major: one 16-byte read per fragment. MN-major: two transposing 8-byte reads, K 0..3 and 4..7
+// of the lane's eight.
 template <bool MN, int G>
 struct Frags {
   static constexpr int kRowB = Sq<G>::W * 2;  // bytes of an MN-major staged row

@@ -50,8 +50,8 @@ struct RowArgs {
   int32_t count_mode;   // 1 (persistent loss calls that write flags, RowLaunch::counts): no
                         // prep_stats; each workgroup counts the valid tokens itself for the
                         // token-mean scale (workgroup 0 stores the count)
-  int32_t flag_counts;  // 1 (calls that write flags): no counter atomics; loss_sum derives the
-                        // counters from the flags
+  int32_t flag_counts;  // 1 (only calls that write flags): no counter atomics; loss_sum derives
+                        // the counters from the flags
 };
 
 // Arguments of the kernels without the backward sweep: the row arguments plus an optional

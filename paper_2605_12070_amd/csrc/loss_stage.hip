@@ -3,15 +3,15 @@
 // small kernels around them (valid-token count, deterministic loss sum).
 //
 // Launch shape: a short row is handled by one wave, a longer one by one workgroup (persistent
-// workgroups loop over rows). A row of V = 151936 bf16 logits (297 KiB) is loaded once with 16-byte loads and
-// kept in registers (1024 threads x 19 x 16 B); the thread's exponentials replace the
-// logits in the same registers as fp16 pairs, so the backward sweep reads nothing from
-// memory and writes dlogits once with 16-byte non-temporal stores. Rows that
-// start or end anywhere are their whole aligned chunks plus a few single entries (for bf16 in
-// variants of their own, the phase kernels). Rows longer than the register budget keep a
-// resident prefix and read only the rest twice (the prefix kernels); what is left (forward
-// calls on rows past the budget, dlogits at another offset within 16 bytes than the logits)
-// uses a streaming kernel that reads the row once per pass.
+// workgroups loop over rows). A row of V = 151936 bf16 logits (297 KiB) is loaded once with
+// 16-byte loads and kept in registers (1024 threads x 19 x 16 B); the thread's exponentials
+// replace the logits in the same registers as fp16 pairs, so the backward sweep reads nothing
+// from memory and writes dlogits once with 16-byte non-temporal stores. Rows that start or end
+// anywhere are their whole aligned chunks plus a few single entries (for bf16 in variants of
+// their own, the phase kernels; short bf16 rows are read as the chunks that cover them). Rows
+// longer than the register budget keep a resident prefix and read only the rest twice (the prefix
+// kernels); what is left (forward calls on rows past the budget, dlogits at another offset within
+// 16 bytes than the logits) uses a streaming kernel that reads the row once per pass.
 #include "dppo.h"
 #include "dppo_device.h"
 #include "loss_stage.h"
@@ -58,11 +58,11 @@ __device__ __forceinline__ bool version_ok(const A& a, int64_t row) {
 // The call's loss scale (Eq. 2: the token-mean normaliser, or the constant), once per
 // workgroup; every thread calls it. Normally prep_stats has stored the valid-token count; in
 // count mode the workgroup counts the mask itself (workgroup 0 also stores the count, for
-// loss_sum), which saves that launch for a short batch. The short-row kernels and the fp32 resident kernel (before
-// their first row) and the bf16 kernels with two row buffers (behind their first row's loads)
-// take this path; in the single-buffer bf16 kernels the extra prologue cost 0.7 % of the
-// flagship's time even with count mode off. Counting behind the first row's loads in the
-// fp32 kernel too was measured slower (the tiny batch's step 27.5 us against 25.6 us).
+// loss_sum), which saves that launch for a short batch. The short-row kernels and the fp32
+// resident kernel (before their first row) and the bf16 kernels with two row buffers (behind
+// their first row's loads) take this path; in the single-buffer bf16 kernels the extra prologue
+// cost 0.7 % of the flagship's time even with count mode off. Counting behind the first row's
+// loads in the fp32 kernel too was measured slower (the tiny batch's step 27.5 us against 25.6).
 template <int NT>
 __device__ float call_scale(const RowArgs& a) {
   if (a.mode == kModeLogprob) return 1.0f;
@@ -1724,7 +1724,8 @@ constexpr int kFillF32Bwd[kNumResident] = {32,   32,   32,   32,   30,   30,   3
 constexpr int kFillF32Fwd[kNumResident] = {32,   32,   32,   32,   32,   32,   32,   27,  27,  27,   32};
 // Measured: bf16 backward and forward; the 256-thread kernels (a row per wave) 32 against 27
 // (2-5 % slower) and 24 (2 % either way); fp32 backward 512 x 4, 512 x 8 and 1024 x 19; fp32
-// forward 512 x 4 and 1024 x 19. fp32 backward 1024 x 6 .. 12 run one workgroup per row (kF32Persistent), so their fill is unused.
+// forward 512 x 4 and 1024 x 19. fp32 backward 1024 x 6 .. 12 run one workgroup per row
+// (kF32Persistent), so their fill is unused.
 constexpr int kFillF32Prefix = 32;
 constexpr int kFillBf16Prefix = 31;
 // Start stagger of the persistent bf16 kernels (RowArgs::stagger: s_sleep(6) units per

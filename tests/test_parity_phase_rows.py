@@ -1,8 +1,8 @@
-"""bf16 rows that do not start on a 16-byte boundary or are not a whole number of 16-byte
-chunks long: the phase kernels read each row as the aligned chunks that cover it and write
-only the row's own entries. Every case compares lp, loss_tok, flags and dlogits with the
-oracle, and checks that every byte of the buffers outside the rows is left as it was
-(the entries between rows, before the first row and after the last)."""
+"""Rows that do not start on a 16-byte boundary or are not a whole number of 16-byte chunks long: the
+kernels take each row as its whole aligned chunks and single entries at its ends (short bf16 rows
+as the chunks that cover them) and write only the row's own entries. Every case compares lp,
+loss_tok, flags and dlogits with the oracle, and checks that every byte of the buffers outside the
+rows is left as it was (the entries between rows, before the first row and after the last)."""
 import numpy as np
 import pytest
 import torch
