@@ -614,6 +614,15 @@ def _scalable(d: torch.Tensor, g: torch.Tensor, dtype: torch.dtype) -> bool:
         return False
 
 
+def _same_rows(rows, d: torch.Tensor) -> bool:
+    """True when rows are the flags and per-token losses of d's tokens, as the scale kernel reads
+    them (a saved-tensor hook may return others)."""
+    return len(rows) == 2 and all(
+        type(t) is torch.Tensor and t.dtype == dt and t.device == d.device
+        and t.shape == d.shape[:1] and t.is_contiguous()
+        for t, dt in zip(rows, (torch.uint8, torch.float32)))
+
+
 class DecoupledPPOLoss(torch.autograd.Function):
     """Autograd wrapper: forward runs the fused kernel (loss and dlogits at once); backward
     returns grad_output * dlogits in one pass, which does not read the rows that the forward's
@@ -624,24 +633,24 @@ class DecoupledPPOLoss(torch.autograd.Function):
                 token_scale, kwargs):
         res = decoupled_ppo_loss_fwd_bwd(logits, token_ids, logp_mu_old, logp_ref, advantages,
                                          loss_mask, token_scale, **(kwargs or {}))
-        ctx.save_for_backward(res.dlogits)
+        # Flags and per-token losses of this call alone; buffers the caller owns (out=) may
+        # hold a later call's by the time of the backward. Saved beside dlogits, so that a
+        # checkpoint that recomputes the forward replaces all three.
+        own = "out" not in (kwargs or {}) and res.flags is not None
+        ctx.save_for_backward(res.dlogits, *((res.flags, res.loss_tok) if own else ()))
         ctx.set_materialize_grads(False)     # no zero fills for logp and stats
         ctx.mark_non_differentiable(res.logp, res.stats)
-        # Flags and per-token losses of this call alone; buffers the caller owns (out=) may
-        # hold a later call's by the time of the backward.
-        own = "out" not in (kwargs or {}) and res.flags is not None
-        ctx.rows = (res.flags, res.loss_tok) if own else None
         ctx.rd_mode = (kwargs or {}).get("rd_mode", "mask_weight")
         return res.loss[0], res.logp, res.stats
 
     @staticmethod
     def backward(ctx, g_loss, g_lp, g_stats):
-        (d,) = ctx.saved_tensors
+        d, *rows = ctx.saved_tensors
         if g_loss is None:
             g_loss = torch.zeros((), dtype=torch.float32, device=d.device)
         if d.dim() == 2 and d.dtype in (torch.bfloat16, torch.float32) and _scalable(d, g_loss, d.dtype):
             T, V = d.shape
-            flags, loss_tok = ctx.rows if ctx.rows is not None else (None, None)
+            flags, loss_tok = rows if _same_rows(rows, d) else (None, None)
             out = torch.empty_like(d)
             st = _lib.lib().dppo_scale_dlogits(
                 d.data_ptr(), _dtype_code(d), T, V, flags.data_ptr() if flags is not None else None,

@@ -10,6 +10,7 @@ import time
 import numpy as np
 import pytest
 import torch
+import torch.utils.checkpoint
 
 import oracle
 import paper_2605_12070_amd as P
@@ -925,3 +926,41 @@ def test_scale_pass_of_short_rows_keeps_pace_with_a_product():
 
     here = us(lambda: L.dppo_scale_dlogits(d.data_ptr(), 1, T, V, None, None, 3, u.data_ptr(), out.data_ptr(), st))
     assert here < 2 * us(lambda: torch.mul(d, u, out=out)), here
+
+
+def test_autograd_backward_under_a_checkpoint_that_recomputes_other_rows():
+    """A checkpointed forward whose second run sees other logits (dropout without the first run's
+    generator state): the gradient is that of the second run, for its own set of zero rows."""
+    wl = W.make_workload("tiny", device=DEV)
+    _say("autograd, checkpoint")
+    g = torch.Generator(device=DEV).manual_seed(2)
+    runs = [wl.logits, wl.logits + torch.randn(wl.T, wl.V, generator=g, device=DEV)]
+    lp = torch.log_softmax(runs[1], dim=1).gather(1, wl.ids[:, None])[:, 0]
+    seen = []
+
+    def f(z):
+        seen.append(len(seen))
+        return P.DecoupledPPOLoss.apply(z + runs[seen[-1]], wl.ids, lp, lp, wl.adv, None, None, None)[0]
+
+    z = torch.zeros_like(wl.logits).requires_grad_(True)
+    torch.utils.checkpoint.checkpoint(f, z, use_reentrant=False).backward()
+    assert seen == [0, 1]
+    first, second = (P.decoupled_ppo_loss_fwd_bwd(r, wl.ids, lp, lp, wl.adv) for r in runs)
+    dead = [r.dlogits.abs().amax(dim=1) == 0 for r in (first, second)]
+    assert (dead[0] & ~dead[1]).any()            # rows whose first flags say zero
+    assert torch.equal(z.grad, second.dlogits)
+
+
+def test_autograd_backward_under_saved_tensor_hooks():
+    """Hooks that keep every saved tensor elsewhere, and ones that bring the flags back in another
+    type (the rows are then all read): the same gradient."""
+    wl = W.make_workload("tiny", device=DEV)
+    lp = torch.log_softmax(wl.logits, dim=1).gather(1, wl.ids[:, None])[:, 0] + 0.1
+    want = 0.5 * P.decoupled_ppo_loss_fwd_bwd(wl.logits, wl.ids, lp, lp, wl.adv).dlogits
+    for pack, unpack in ((lambda t: t.cpu(), lambda t: t.to(DEV)), (lambda t: t.float(), lambda t: t)):
+        _say("autograd, hooks")
+        z = wl.logits.clone().requires_grad_(True)
+        with torch.autograd.graph.saved_tensors_hooks(pack, unpack):
+            loss = P.DecoupledPPOLoss.apply(z, wl.ids, lp, lp, wl.adv, None, None, None)[0]
+        (0.5 * loss).backward()
+        assert torch.equal(z.grad, want)
