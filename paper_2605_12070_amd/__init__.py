@@ -600,13 +600,12 @@ def _scalable(d: torch.Tensor, g: torch.Tensor, dtype: torch.dtype) -> bool:
     device, outside a differentiated backward (create_graph) and outside vmap or tracing, whose
     tensors have no data pointer. A lazily negated tensor (the imaginary part of a conjugate)
     holds the other sign in memory."""
-    if torch.is_grad_enabled() or type(d) is not torch.Tensor or type(g) is not torch.Tensor:
+    if (torch.is_grad_enabled() or type(d) is not torch.Tensor or type(g) is not torch.Tensor
+            or d.dtype is not dtype or g.dtype is not torch.float32 or g.dim() != 0
+            or d.is_neg() or g.is_neg() or not (d.is_cuda and g.is_cuda) or not d.is_contiguous()):
         return False
-    if d.is_neg() or g.is_neg():
-        return False
-    if (d.dtype != dtype or g.dtype != torch.float32 or g.dim() != 0 or not d.is_cuda
-            or d.device != g.device or d.device.index != torch.cuda.current_device()
-            or not d.is_contiguous()):
+    dev = d.get_device()
+    if g.get_device() != dev or dev != torch._C._cuda_getDevice():
         return False
     try:
         return d.data_ptr() % 16 == 0 and g.data_ptr() != 0
@@ -617,10 +616,15 @@ def _scalable(d: torch.Tensor, g: torch.Tensor, dtype: torch.dtype) -> bool:
 def _same_rows(rows, d: torch.Tensor) -> bool:
     """True when rows are the flags and per-token losses of d's tokens, as the scale kernel reads
     them (a saved-tensor hook may return others)."""
-    return len(rows) == 2 and all(
-        type(t) is torch.Tensor and t.dtype == dt and t.device == d.device
-        and t.shape == d.shape[:1] and t.is_contiguous()
-        for t, dt in zip(rows, (torch.uint8, torch.float32)))
+    if len(rows) != 2:
+        return False
+    f, lt = rows
+    T = d.shape[0]
+    dev = d.get_device()
+    return (type(f) is type(lt) is torch.Tensor and f.dtype is torch.uint8
+            and lt.dtype is torch.float32 and f.is_cuda and lt.is_cuda
+            and f.get_device() == lt.get_device() == dev and f.numel() == lt.numel() == T
+            and f.is_contiguous() and lt.is_contiguous())
 
 
 class DecoupledPPOLoss(torch.autograd.Function):
