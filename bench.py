@@ -39,7 +39,7 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("dppo_device.h", "loss_stage.h", "token_math.h", "loss_stage.hip")
+KERNEL_SOURCES = ("dppo_device.h", "loss_stage.h", "token_math.h", "row_split.h", "loss_stage.hip")
 SHARD_SOURCES = ("dppo_device.h", "loss_stage.h", "token_math.h", "vocab_shard.h",
                  "vocab_shard.hip")
 EWMA_SOURCES = ("dppo_device.h", "ewma.h", "ewma.hip")
@@ -377,8 +377,8 @@ def lm_head_measure(dev, reps=5):
     del out, wl
     return {"bound": "mfma", "achieved": round(achieved, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
-            "kernel": "dppo::lmh_fwd_tiles / dppo::lmh_grad_gemm<false, true> (dhidden) / "
-                      "dppo::lmh_grad_gemm<true, true> (dW), mean per launch",
+            "kernel": "dppo::lmh_fwd_tiles / dppo::lmh_grad_gemm<false, true, false, 4> (dhidden) / "
+                      "dppo::lmh_grad_gemm<true, true, false, 4> (dW), mean per launch",
             "kernel_ms": round(prod_ms, 3), "alg_flops_per_launch": prod_flops,
             "workload": f"lm_head T={T} d={d} V={V} bf16, both gradients, one-pass backward",
             "call_ms": round(call_ms, 3), "tokens_per_s": round(T / (call_ms * 1e-3), 1),
