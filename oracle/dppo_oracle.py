@@ -1,6 +1,6 @@
 """Plain float64 CPU oracle for the per-token loss stage of decoupled off-policy PPO.
 
-TEST INFRASTRUCTURE. This module is the checker, not the product. Only the tests, the
+TEST INFRASTRUCTURE. This module is the oracle, not the product. Only the tests, the
 smoke check and the benchmark's CPU-baseline leg may import or run it; the library path
 never does. It shares no code, constant or helper with the HIP path and imports nothing
 from the package.
