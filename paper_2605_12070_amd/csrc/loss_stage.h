@@ -91,6 +91,8 @@ constexpr int kPrefixNC = 19;  // resident 16-byte chunks per thread of the pref
 constexpr int kPrefixKeepF32 = 9;
 // and the bf16 prefix kernel, beside its 76 KB shift table
 constexpr int kPrefixKeepBf16 = 5;
+// and the bf16 prefix kernel for rows that start anywhere, which has no such table
+constexpr int kPrefixKeepBf16Phase = 7;
 
 // aligned: the rows (and dlogits rows) start on 16-byte boundaries. phase_ok: rows that start
 // on any entry's own boundary, with dlogits (if any) at the logits' phase on every row (the

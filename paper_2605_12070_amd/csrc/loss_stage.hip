@@ -1391,16 +1391,17 @@ __global__ __launch_bounds__(NT) void rows_f32_prefix(RowArgs a) {
 // the run-time offset cost the aligned rows 2 %.) Their resident chunks stay logits, and the whole
 // gradient is formed from them in fp32, as the streaming kernel forms it: fp16 exponentials would
 // round once more and lose the entries below 2^-24 of their chunk's maximum. No shift table then,
-// so the next KS = 9 chunks of a thread wait in LDS. T = 2048: V = 155661 290 us (fp16
-// exponentials 287, streaming entry by entry 1113), V = 262143 504 us (485, 2043), V = 400001
-// 743 us (746, 3388).
+// so there is room for KS = 9 chunks of a thread in LDS; 7 of them measure best. With fp16
+// exponentials, and with 5, 7 and 9 (us): T = 2048, V = 200001 373, 379, 380, 384 (streaming entry
+// by entry 1504); T = 5000, V = 230001 981, 1017, 1000, 1034; T = 4096, V = 262143 930, 947, 942, 949;
+// T = 8192, V = 180001 1211, 1225, 1218, 1224; T = 3001, V = 400001 1081, 1098, 1098, 1079.
 template <int NT, int NC, bool PH>
 __device__ __forceinline__ void bf16_prefix_rows(const RowArgs& a) {
   constexpr int P = NT * NC;              // resident chunks of a row
   constexpr int U = 4;                    // tail chunks per thread in flight
   // the first KS of each thread's tail chunks also wait in LDS between the passes (each
   // thread reads back only what it wrote), beside the shift table
-  constexpr int KS = PH ? kPrefixKeepF32 : kPrefixKeepBf16;
+  constexpr int KS = PH ? kPrefixKeepBf16Phase : kPrefixKeepBf16;
   __shared__ float red[2 * (NT / 64) + 2];
   __shared__ Bcast bc;
   __shared__ float nch[PH ? 1 : NC][NT];  // per-chunk shifts, [c][tid]: conflict-free
