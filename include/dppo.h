@@ -461,8 +461,9 @@ dppo_status dppo_reset_decision(const int32_t* stats, double tau, int32_t patien
  *
  * dppo_scale_dlogits -- out = dlogits * g, both [T, V] of `dtype`, contiguous and 16-byte
  *   aligned; g is rounded to `dtype` first. With flags (the loss call's flags_out; rd_mode and
- *   loss_tok are then that call's too) a row that is zero in dlogits because its token is
- *   masked, bad, clipped or out of band is not read and written as 0 * g. out may be dlogits.
+ *   loss_tok are then that call's too) rows that are zero in dlogits because their tokens are
+ *   masked, bad, clipped or out of band are written as 0 * g, and 16-byte chunks that lie in
+ *   such rows alone are not read. out may be dlogits.
  * dppo_scale_to_bf16 -- dst = bf16(src * g) for n float32 values; both 16-byte aligned.
  *   g: device float32 scalar.
  */
